@@ -31,6 +31,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace bdfx {
 
 constexpr int kWave = 64;
@@ -124,6 +126,11 @@ struct Params {
   int32_t ldp;
 };
 
+struct LaunchCfg {
+  int grid, block;
+  size_t lds_bytes;
+};
+
 // ---------------------------------------------------------------------------
 // wavefront primitives (all 64 lanes active, uniform control flow)
 // ---------------------------------------------------------------------------
@@ -135,6 +142,13 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
+
+// A point all lanes reach together: control flow that depends on the lane cannot
+// be carried across it.  The sums that reactions scatter into LDS take their
+// terms in the order of the instructions and, within one, of the lanes; a
+// compiler that splits the lanes of a partly filled pass off into a copy of the
+// code that follows would change that order, and with it the last bits.
+__device__ __forceinline__ void lanes_meet() { __builtin_amdgcn_wave_barrier(); }
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -363,6 +377,17 @@ struct Grp {
   }
 };
 
+// The same lane group with a lane index the optimizer cannot trace: addresses
+// formed from it are computed where they are used instead of being hoisted out
+// of the integration's loops and kept in registers (at 53 species that held
+// some 30 VGPRs through the elimination, as much as it then spilled).
+template <int G>
+__device__ __forceinline__ Grp<G> local_lane(const Grp<G> &W) {
+  Grp<G> V = W;
+  asm volatile("" : "+v"(V.lane));
+  return V;
+}
+
 // ---------------------------------------------------------------------------
 // Nordsieck array operations (z_j = h^j y^(j) / j!)
 // ---------------------------------------------------------------------------
@@ -372,8 +397,14 @@ struct Grp {
 // zeroes z_2..), so the operations below run over all kQmax columns with no
 // per-order selects: the extra terms add or scale exact zeros.
 
+// Sums whose operands may come out of a product on one path (a rescaled column, a
+// scaled correction) are formed without contraction: whether the compiler can
+// see that product next to the sum depends on how it lays out the branches, and
+// every kernel has to give the same bits.
+
 // z <- z * Pascal: Taylor shift by one step (predictor).
 __device__ __forceinline__ void nd_predict(double (&z)[kQmax + 1]) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int k = 1; k <= kQmax; ++k)
 #pragma unroll
@@ -382,10 +413,16 @@ __device__ __forceinline__ void nd_predict(double (&z)[kQmax + 1]) {
 
 // exact inverse of nd_predict (restore after a rejected attempt)
 __device__ __forceinline__ void nd_unpredict(double (&z)[kQmax + 1]) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int k = 1; k <= kQmax; ++k)
 #pragma unroll
     for (int j = kQmax; j >= k; --j) z[j - 1] -= z[j];
+}
+
+__device__ __forceinline__ double plain_sum(double a, double b) {
+#pragma clang fp contract(off)
+  return a + b;
 }
 
 // h -> eta h: z_j <- eta^j z_j
@@ -426,6 +463,43 @@ __device__ __forceinline__ void bdf_coeffs(int q, const double (&xi)[kQmax + 2],
       for (int j = i; j >= 1; --j) l[j] = fma(l[j - 1], rxi, l[j]);
     }
   Cerr = rcp(l[1] * pick(xi, q + 1));
+}
+
+// xi_i and l_j of an attempt with step h and order q, into the control block C
+// (after the step sizes hist[0..] it holds), one lane per index: lane i forms
+// xi_i = (h + h_1 + ... + h_{i-1}) / h and its reciprocal, lane j the
+// coefficient l_j, which takes the factors (1 + x/xi_i) in turn from its
+// neighbour's.  The operations of bdf_coeffs on each entry.  Every lane gets
+// l_1 and Cerr.
+template <int G>
+__device__ __forceinline__ void step_coeffs(int q, double h, double *C, const double *hist, int kxi,
+                                            int kl, const Grp<G> &W, double &l1, double &Cerr) {
+  const int i = local_lane(W).lane;
+  double sum = h;
+#pragma unroll
+  for (int k = 0; k <= kQmax - 1; ++k) {
+    const double hk = hist[k];
+    sum = plain_sum(sum, i >= k + 2 ? hk : 0.0);
+  }
+  const double rh = rcp(h);
+  double xi = sum * rh;
+  if (i > q + 1 || i == 0) xi = 0.0;
+  if (i == 1) xi = 1.0;
+  const double rxi = rcp(xi);
+  double l = i == 0 ? 1.0 : 0.0;
+#pragma unroll
+  for (int k = 1; k <= kQmax; ++k)
+    if (k <= q) {
+      const double below = dpp<0x111, 0xf>(l);  // row_shr:1
+      l = fma(i == 0 ? 0.0 : below, W.bcast(rxi, k), l);
+    }
+  wave_lds_sync();
+  if (i <= kQmax + 1) {
+    C[kxi + i] = xi;
+    C[kl + i] = l;
+  }
+  l1 = W.uni(W.bcast(l, 1));
+  Cerr = W.uni(rcp(l1 * W.bcast(xi, q + 1)));
 }
 
 // H_k = 1 + 1/2 + ... + 1/k and k! for k = 0..6
@@ -714,48 +788,174 @@ __device__ __forceinline__ void thermal_rates(const MechDev &m, const Lds &L, in
 // Non-isothermal cells (TH): lane ns (= the species count) holds the
 // temperature; the rate constants are evaluated at it, and that lane gets
 // dT/dt = F_T - sum_i u_i(T) f_i / sum_i cv_i y_i.
-template <bool ABC, bool TH = false, int G>
+//
+// NP: passes whose table entries are loaded at once, the first NP before the
+// state is exchanged.  With the tables in global memory (NP = 6, all of a
+// 325-reaction mechanism) a right-hand side then waits for memory once instead
+// of once per two passes.
+template <bool ABC, bool TH = false, int NP = 2, int G>
 __device__ __forceinline__ double rhs(const MechDev &m, const Lds &L, const Grp<G> &W, double yi,
                                       double Fi, int ns = 0) {
-  wave_lds_sync();
-  L.yb[W.lane] = yi;
-  L.fb[W.lane] = Fi;
-  wave_lds_sync();
   const int R = m.R;
+  int2 w[NP];
+  double k[NP][2];
+  const int lane = local_lane(W).lane;
+  auto load = [&](int r0) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = r0 + p * W.kLanes + lane;
+      w[p] = make_int2(0x40404040, 0x40404040);  // every slot empty
+      if (r < R) {
+        w[p] = L.rx[r];
+        if constexpr (!TH) {
+          k[p][0] = L.kk[2 * r];
+          k[p][1] = L.kk[2 * r + 1];
+        }
+      }
+    }
+  };
+  load(0);
+  wave_lds_sync();
+  L.yb[lane] = yi;
+  L.fb[lane] = Fi;
+  wave_lds_sync();
   double rT = 0.0;
   if constexpr (TH) rT = W.uni(rcp(W.bcast(yi, ns)));
-  const int2 none = make_int2(0x40404040, 0x40404040);  // every slot empty
-  for (int r0 = 0; r0 < R; r0 += 2 * W.kLanes) {
-    const int ra = r0 + W.lane, rb = ra + W.kLanes;
-    const int2 wa = ra < R ? L.rx[ra] : none;
-    const int2 wb = rb < R ? L.rx[rb] : none;
-    if constexpr (TH) {
-      if (ra < R) {
-        double kf, krn;
-        thermal_rates(m, L, ra, rT, kf, krn);
-        rhs_reaction<ABC>(L, ra, wa, kf, krn);
+  for (int r0 = 0;;) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = r0 + p * W.kLanes + lane;
+      if (r < R) {
+        if constexpr (TH) thermal_rates(m, L, r, rT, k[p][0], k[p][1]);
+        rhs_reaction<ABC>(L, r, w[p], k[p][0], k[p][1]);
       }
-      if (rb < R) {
-        double kf, krn;
-        thermal_rates(m, L, rb, rT, kf, krn);
-        rhs_reaction<ABC>(L, rb, wb, kf, krn);
-      }
-    } else {
-      if (ra < R) rhs_reaction<ABC>(L, ra, wa, L.kk[2 * ra], L.kk[2 * ra + 1]);
-      if (rb < R) rhs_reaction<ABC>(L, rb, wb, L.kk[2 * rb], L.kk[2 * rb + 1]);
+      lanes_meet();
     }
+    r0 += NP * W.kLanes;
+    if (r0 >= R) break;
+    load(r0);
   }
   wave_lds_sync();
   if constexpr (TH) {
-    const double f = L.fb[W.lane];
-    const bool sp = W.lane < ns;
+    const double f = L.fb[lane];
+    const bool sp = lane < ns;
     const double T = W.uni(W.bcast(yi, ns));
-    const double cv = sp ? m.cv[W.lane] : 0.0, u = sp ? fma(cv, T, m.u0[W.lane]) : 0.0;
+    const double cv = sp ? m.cv[lane] : 0.0, u = sp ? fma(cv, T, m.u0[lane]) : 0.0;
     const double N = W.uni(W.sum(u * f)), D = W.uni(W.sum(cv * yi));
-    return W.lane == ns ? f - N / D : f;
+    return lane == ns ? f - N / D : f;
   }
-  return L.fb[W.lane];
+  return L.fb[lane];
 }
+
+// ---------------------------------------------------------------------------
+// the Newton matrix in registers
+// ---------------------------------------------------------------------------
+
+// Row i in lane i (gj_invert below): at most 16 species, or two cells per wave.
+template <int S, typename LT>
+struct RowMat {
+  LT a[S];
+  // columns c0 .. c0 + nc - 1 from LDS, column c at (c - c0) * S (rows, not
+  // columns, at that stride when transposed)
+  template <int G>
+  __device__ __forceinline__ void read(const LT *M, const Grp<G> &W, int c0, int nc, bool transposed = false) {
+    const int lr = W.lane < S ? W.lane : 0;
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      if (j < c0 || j >= c0 + nc) continue;
+      const LT v = transposed ? M[lr * S + j] : M[(j - c0) * S + lr];
+      a[j] = W.lane < S ? v : static_cast<LT>(0);
+    }
+  }
+};
+
+// Matrix-core tiles (mx_invert below): x[T][C][t] of lane j + 16 g is the entry
+// of row 16 C + j and column 16 T + 4 t + g, so that four consecutive columns
+// (one t) fill the 64 lanes of NT registers.
+template <typename LT>
+struct Mx;
+template <>
+struct Mx<double> {
+  typedef double V __attribute__((ext_vector_type(4)));
+  // register t of lane group g of a result tile is its row 4 t + g
+  static __device__ __forceinline__ V mma(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  // the column (within a tile) that row i of the first operand stands for
+  static __device__ __forceinline__ int col(int i) { return i; }
+};
+template <>
+struct Mx<float> {
+  typedef float V __attribute__((ext_vector_type(4)));
+  // register t of lane group g of a result tile is its row 4 g + t
+  static __device__ __forceinline__ V mma(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int col(int i) { return 4 * (i & 3) + (i >> 2); }
+};
+
+template <int S, typename LT>
+struct TileMat {
+  static constexpr int NT = S <= 32 ? 2 : 4;
+  typedef typename Mx<LT>::V V;
+  V x[NT][NT];
+  // as RowMat::read; c0 is a multiple of 4.  Four base addresses (the last, partly
+  // filled rows and columns read a clamped entry and take 0), the rest of every
+  // address is an instruction offset.
+  template <int G>
+  __device__ __forceinline__ void read(const LT *M, const Grp<G> &W, int c0, int nc, bool transposed = false) {
+    constexpr int RE = (S - 1) / 16, CE = (S - 1) / 4;  // tile row, column group of the last entry
+    const int j = W.lane & 15, g = W.lane >> 4;
+    const int sc = transposed ? 1 : S, sr = transposed ? S : 1;  // strides of columns and rows
+    const bool jin = 16 * RE + j < S, gin = 4 * CE + g < S;
+    const int je = jin ? j : S - 1 - 16 * RE, ge = gin ? g : S - 1 - 4 * CE;
+    const LT *base[2][2] = {{M + g * sc + j * sr, M + g * sc + je * sr},
+                            {M + ge * sc + j * sr, M + ge * sc + je * sr}};
+#pragma unroll
+    for (int T = 0; T < NT; ++T)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int q = 4 * T + t;  // columns 4 q .. 4 q + 3
+        if (q > CE) {
+#pragma unroll
+          for (int C = 0; C < NT; ++C) x[T][C][t] = static_cast<LT>(0);
+          continue;
+        }
+        if (4 * q < c0 || 4 * q >= c0 + nc) continue;
+#pragma unroll
+        for (int C = 0; C < NT; ++C) {
+          if (C > RE) {
+            x[T][C][t] = static_cast<LT>(0);
+            continue;
+          }
+          const LT v = base[q == CE][C == RE][(4 * q - c0) * sc + 16 * C * sr];
+          const bool in = (q < CE || gin) && (C < RE || jin);
+          x[T][C][t] = in ? v : static_cast<LT>(0);
+        }
+      }
+  }
+};
+
+// Columns c0 .. c0 + NC - 1 of the identity, column c at (c - c0) * S.
+template <int S, int NC, typename LT, int G>
+__device__ __forceinline__ void write_identity(LT *M, const Grp<G> &W, int c0) {
+  constexpr int L = Grp<G>::kLanes, N = NC * S;
+#pragma unroll
+  for (int e = 0; e + L <= N; e += L) M[e + W.lane] = static_cast<LT>(0);
+  if (N % L && W.lane < N % L) M[N / L * L + W.lane] = static_cast<LT>(0);
+  if (W.lane >= c0 && W.lane < c0 + NC) M[(W.lane - c0) * S + W.lane] = static_cast<LT>(1);
+}
+
+template <int S, typename LT, bool TILED>
+struct MatOf {
+  typedef RowMat<S, LT> type;
+};
+template <int S, typename LT>
+struct MatOf<S, LT, true> {
+  typedef TileMat<S, LT> type;
+};
+template <int S, typename LT, int G>
+using Mat = typename MatOf<S, LT, (G == 1 && S > 16)>::type;
 
 // Row li of M = I - gamma J (or of M^T when `transposed`) at the state y held
 // by the lanes (lane i passes y_i).  M is assembled in LDS, in the area that
@@ -770,31 +970,33 @@ __device__ __forceinline__ double rhs(const MechDev &m, const Lds &L, const Grp<
 // whose LDS area holds S - T columns): two passes over the reactions, columns
 // 0 .. S-T-1 and then the last T, each entry with the same terms in the same
 // order as in one pass.
-template <int S, typename LT, bool ABC = false, int T = 0, int G>
-__device__ __forceinline__ void newton_matrix(LT (&a)[S], const MechDev &m, const Lds &L, const Grp<G> &W,
+// YSET > 0 (kernels with several cells per wave): L.yb holds the state already
+// and empty slots carry the index YSET.
+template <int S, typename LT, bool ABC = false, int T = 0, int YSET = 0, int G>
+__device__ __forceinline__ void newton_matrix(Mat<S, LT, G> &a, const MechDev &m, const Lds &L, const Grp<G> &W,
                                               double yi, double gamma, bool transposed) {
+  const Grp<G> V = local_lane(W);
   static_assert(T == 0 || G == 1, "an inverse tail needs one cell per wave");
   LT *M = reinterpret_cast<LT *>(L.fac);
-  const int lr = W.lane < S ? W.lane : 0;
+  constexpr int kEmpty = YSET > 0 ? YSET : kEmptySlot;
   wave_lds_sync();
-  L.yb[W.lane] = yi;
+  if constexpr (YSET == 0) L.yb[V.lane] = yi;
 #pragma unroll
   for (int pass = 0; pass < (T > 0 ? 2 : 1); ++pass) {
     // columns c0 .. c0 + nc - 1, column c at (c - c0) * S
     const int c0 = pass == 0 ? 0 : S - T, nc = T == 0 ? S : (pass == 0 ? S - T : T);
     if (pass > 0) wave_lds_sync();
-    for (int e = W.lane; e < nc * S; e += W.kLanes)
-      M[e] = e % S == c0 + e / S ? static_cast<LT>(1) : static_cast<LT>(0);
+    if (pass == 0) write_identity<S, S - T>(M, V, 0);
+    else write_identity<S, (T > 0 ? T : 1)>(M, V, S - T);
     wave_lds_sync();
-    for (int r = W.lane; r < m.R; r += W.kLanes) {
-      const int2 w = L.rx[r];
+    auto scatter = [&](int2 wr, double kf_r, double kr_r) {
       if constexpr (ABC) {
         // columns A, B (forward side) and C (reverse side), each scattered
         // into rows A, C, B: the generic path's terms in its order
-        const int a0 = slot_species(w.x, 0), a1 = slot_species(w.x, 1), b0 = slot_species(w.y, 0);
-        const double kf = L.kk[2 * r];
+        const int a0 = slot_species(wr.x, 0), a1 = slot_species(wr.x, 1), b0 = slot_species(wr.y, 0);
+        const double kf = kf_r;
         const int col[3] = {a0, a1, b0};
-        const double d[3] = {kf * L.yb[a1], kf * L.yb[a0], L.kk[2 * r + 1]};
+        const double d[3] = {kf * L.yb[a1], kf * L.yb[a0], kr_r};
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           if (c == 2 && !m.reversible) break;
@@ -807,22 +1009,22 @@ __device__ __forceinline__ void newton_matrix(LT (&a)[S], const MechDev &m, cons
           atomicAdd(Mc + b0, -g);
           atomicAdd(Mc + a1, g);
         }
-        continue;
+        return;
       }
       int sp[2][3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        sp[0][k] = slot_species(w.x, k);
-        sp[1][k] = slot_species(w.y, k);
+        sp[0][k] = slot_species(wr.x, k);
+        sp[1][k] = slot_species(wr.y, k);
       }
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
         if (side == 1 && !m.reversible) break;
-        const double kside = L.kk[2 * r + side];
+        const double kside = side == 0 ? kf_r : kr_r;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const int col = sp[side][c];
-          if (col == kEmptySlot) continue;
+          if (col == kEmpty) continue;
           if constexpr (T > 0) {
             if (col < c0 || col >= c0 + nc) continue;
           }
@@ -834,19 +1036,34 @@ __device__ __forceinline__ void newton_matrix(LT (&a)[S], const MechDev &m, cons
           LT *Mc = M + (col - c0) * S;
 #pragma unroll
           for (int i = 0; i < 3; ++i) {
-            if (sp[0][i] != kEmptySlot) atomicAdd(Mc + sp[0][i], g);
-            if (sp[1][i] != kEmptySlot) atomicAdd(Mc + sp[1][i], -g);
+            if (sp[0][i] != kEmpty) atomicAdd(Mc + sp[0][i], g);
+            if (sp[1][i] != kEmpty) atomicAdd(Mc + sp[1][i], -g);
           }
         }
       }
+    };
+    // (the next reaction's table entries are loaded while this one is scattered:
+    // they may come from global memory)
+    int2 w = make_int2(0, 0);
+    double kfn = 0.0, krn = 0.0;
+    auto load = [&](int r) {
+      if (r < m.R) {
+        w = L.rx[r];
+        kfn = L.kk[2 * r];
+        krn = L.kk[2 * r + 1];
+      }
+    };
+    load(V.lane);
+    for (int r0 = 0; r0 < m.R; r0 += W.kLanes) {
+      const int2 wr = w;
+      const double kf_r = kfn, kr_r = krn;
+      load(r0 + W.kLanes + V.lane);
+      lanes_meet();
+      if (r0 + V.lane < m.R) scatter(wr, kf_r, kr_r);
+      lanes_meet();
     }
     wave_lds_sync();
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-      if (j < c0 || j >= c0 + nc) continue;
-      const LT v = (T == 0 && transposed) ? M[lr * S + j] : M[(j - c0) * S + lr];
-      a[j] = W.lane < S ? v : static_cast<LT>(0);
-    }
+    a.read(M, V, c0, nc, T == 0 && transposed);
   }
   wave_lds_sync();
 }
@@ -865,7 +1082,7 @@ __device__ __forceinline__ void newton_matrix(LT (&a)[S], const MechDev &m, cons
 //   M(T, j) = gamma (sum_r dU_r dq_r/dy_j - N cv_j / D) / D,
 //   M(T, T) = 1 + gamma (sum_i cv_i f_i + sum_r dU_r dq_r/dT) / D.
 template <int S, typename LT, int G>
-__device__ __forceinline__ void newton_matrix_thermal(LT (&a)[S], const MechDev &m, const Lds &L,
+__device__ __forceinline__ void newton_matrix_thermal(Mat<S, LT, G> &a, const MechDev &m, const Lds &L,
                                                    const Grp<G> &W, double yi, double Fi,
                                                    double gamma, int ns) {
   LT *M = reinterpret_cast<LT *>(L.fac);
@@ -880,10 +1097,9 @@ __device__ __forceinline__ void newton_matrix_thermal(LT (&a)[S], const MechDev 
   L.uT[W.lane] = u;  // 0 past the species
   if (W.lane == 0) L.uT[kEmptySlot] = 0.0;
   L.uj[W.lane] = 0.0;
-  for (int e = W.lane; e < S * S; e += W.kLanes)
-    M[e] = e % (S + 1) == 0 ? static_cast<LT>(1) : static_cast<LT>(0);
+  write_identity<S, S>(M, W, 0);
   wave_lds_sync();
-  for (int r = W.lane; r < m.R; r += W.kLanes) {
+  auto scatter = [&](int r) {
     const int2 w = L.rx[r];
     double kf, krn;
     thermal_rates(m, L, r, rT, kf, krn);
@@ -935,6 +1151,10 @@ __device__ __forceinline__ void newton_matrix_thermal(LT (&a)[S], const MechDev 
         atomicAdd(&L.uj[col], d * dU);
       }
     }
+  };
+  for (int r0 = 0; r0 < m.R; r0 += W.kLanes) {
+    if (r0 + W.lane < m.R) scatter(r0 + W.lane);
+    lanes_meet();
   }
   wave_lds_sync();
   const double f = L.fb[W.lane];
@@ -947,12 +1167,7 @@ __device__ __forceinline__ void newton_matrix_thermal(LT (&a)[S], const MechDev 
     M[W.lane * S + ns] = static_cast<LT>(v);
   }
   wave_lds_sync();
-  const int lr = W.lane < S ? W.lane : 0;
-#pragma unroll
-  for (int j = 0; j < S; ++j) {
-    const LT v = M[j * S + lr];
-    a[j] = W.lane < S ? v : static_cast<LT>(0);
-  }
+  a.read(M, W, 0, S);
   wave_lds_sync();
 }
 
@@ -972,7 +1187,7 @@ __device__ __forceinline__ double wrms2(const Grp<G> &W, double v, double w, dou
 // written to the LDS matrix area (padding entries keep the identity), then
 // each lane reads its row.  Costs n + 1 right-hand sides.
 template <int S, typename LT, bool ABC, bool TH, int G>
-__device__ __forceinline__ void dq_matrix(LT (&a)[S], const MechDev &m, const Lds &L, const Grp<G> &W,
+__device__ __forceinline__ void dq_matrix(Mat<S, LT, G> &a, const MechDev &m, const Lds &L, const Grp<G> &W,
                                           double y, double Fi, double gamma, double h, double ewt,
                                           int ns, int n, double inv_n) {
   LT *M = reinterpret_cast<LT *>(L.fac);
@@ -993,8 +1208,7 @@ __device__ __forceinline__ void dq_matrix(LT (&a)[S], const MechDev &m, const Ld
       const double fnorm = W.uni(sqrt(wrms2<S>(W, f0, ewt, inv_n)));
       min_inc = fnorm != 0.0 ? 1000.0 * fabs(h) * kUround * n * fnorm : 1.0;
       wave_lds_sync();
-      for (int e = W.lane; e < S * S; e += W.kLanes)
-        M[e] = e % (S + 1) == 0 ? static_cast<LT>(1) : static_cast<LT>(0);
+      write_identity<S, S>(M, W, 0);
     } else {
       const double col = (f - f0) / inc;
       wave_lds_sync();
@@ -1002,12 +1216,7 @@ __device__ __forceinline__ void dq_matrix(LT (&a)[S], const MechDev &m, const Ld
     }
   }
   wave_lds_sync();
-  const int lr = W.lane < S ? W.lane : 0;
-#pragma unroll
-  for (int j = 0; j < S; ++j) {
-    const LT v = M[j * S + lr];
-    a[j] = W.lane < S ? v : static_cast<LT>(0);
-  }
+  a.read(M, W, 0, S);
   wave_lds_sync();
 }
 
@@ -1174,9 +1383,10 @@ __device__ __forceinline__ void gj_block(LT (&a)[S], const Grp<G> &W, int k0, in
 // Returns 0, or k+1 for the first column k without a nonzero pivot (the
 // elimination then runs on garbage).
 template <int S, typename LT, int T = 0, int G>
-__device__ __forceinline__ int gj_invert(LT (&a)[S], const Grp<G> &W, const Lds &L,
-                                         InvTail<T, LT> *tail = nullptr) {
-  static_assert(T == 0 || (G == 1 && sizeof(LT) == 8), "an inverse tail: FP64, one cell per wave");
+__device__ __forceinline__ int invert(RowMat<S, LT> &m, const Grp<G> &W, const Lds &L, int n,
+                                      InvTail<T, LT> *tail = nullptr) {
+  static_assert(T == 0, "an inverse tail needs the tiled form");
+  LT (&a)[S] = m.a;
   // steps per block (one register rotation per block): eight above 32
   // species, where the rotation's S moves are a larger share; sixteen
   // steps made the 53-species FP64 kernels' loop too large for the
@@ -1195,20 +1405,341 @@ __device__ __forceinline__ int gj_invert(LT (&a)[S], const Grp<G> &W, const Lds 
   wave_lds_sync();
   if (W.lane < S) perm[piv] = W.lane;
   wave_lds_sync();
-  if constexpr (T == 0) {
-    if (W.lane < S) {
+  if (W.lane < S) {
 #pragma unroll
-      for (int k = 0; k < S; ++k) inv[perm[k] * S + piv] = a[k] * dinv;
-    }
+    for (int k = 0; k < S; ++k) inv[perm[k] * S + piv] = a[k] * dinv;
+  }
+  wave_lds_sync();
+  return info;
+}
+
+// ---------------------------------------------------------------------------
+// Gauss-Jordan on matrix-core tiles
+// ---------------------------------------------------------------------------
+
+__device__ __forceinline__ void swap16(int &a, int &b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = static_cast<int>(r[0]);
+  b = static_cast<int>(r[1]);
+}
+__device__ __forceinline__ void swap32(int &a, int &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = static_cast<int>(r[0]);
+  b = static_cast<int>(r[1]);
+}
+// Exchanges the odd 16-lane rows of a with the even ones of b (W16), or the
+// upper 32 lanes of a with the lower ones of b.
+template <bool W16>
+__device__ __forceinline__ void swap_rows(double &a, double &b) {
+  int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
+  if constexpr (W16) {
+    swap16(x.x, y.x);
+    swap16(x.y, y.y);
   } else {
-    if (W.lane < S) {
+    swap32(x.x, y.x);
+    swap32(x.y, y.y);
+  }
+  a = __builtin_bit_cast(double, x);
+  b = __builtin_bit_cast(double, y);
+}
+template <bool W16>
+__device__ __forceinline__ void swap_rows(float &a, float &b) {
+  int x = __builtin_bit_cast(int, a), y = __builtin_bit_cast(int, b);
+  if constexpr (W16) swap16(x, y);
+  else swap32(x, y);
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
+}
+
+// The 4 x 4 transposition of registers and 16-lane rows: row g of register c
+// becomes row c of register g (its own inverse).
+template <typename LT>
+__device__ __forceinline__ void transpose4(LT (&r)[4]) {
+  swap_rows<false>(r[0], r[2]);
+  swap_rows<false>(r[1], r[3]);
+  swap_rows<true>(r[0], r[1]);
+  swap_rows<true>(r[2], r[3]);
+}
+
+// Four columns between the tile form (register C: rows 16 C .. 16 C + 15,
+// column g in 16-lane row g) and one register per column with one matrix row per
+// lane.  NT = 2: 32 matrix rows, held twice.
+template <int NT, typename LT>
+__device__ __forceinline__ void to_rows(const LT (&r)[NT], LT (&p)[4]) {
+  if constexpr (NT == 4) {
 #pragma unroll
-      for (int k = 0; k < S - T; ++k) inv[k * S + piv] = a[k] * dinv;
+    for (int k = 0; k < 4; ++k) p[k] = r[k];
+    transpose4(p);
+  } else {
+    LT a = r[0], b = r[1];
+    swap_rows<true>(a, b);  // a: columns 0 and 2, b: 1 and 3
+    p[0] = p[2] = a;
+    swap_rows<false>(p[0], p[2]);
+    p[1] = p[3] = b;
+    swap_rows<false>(p[1], p[3]);
+  }
+}
+template <int NT, typename LT>
+__device__ __forceinline__ void to_tiles(const LT (&p)[4], LT (&r)[NT], bool low) {
+  if constexpr (NT == 4) {
+    LT q[4] = {p[0], p[1], p[2], p[3]};
+    transpose4(q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = q[k];
+  } else {
+    LT a = low ? p[0] : p[2], b = low ? p[1] : p[3];
+    swap_rows<true>(a, b);
+    r[0] = a;
+    r[1] = b;
+  }
+}
+
+// Pivot search and elimination of column E of a panel of four columns (one
+// matrix row per lane; the arithmetic of gj_step): q receives the multipliers,
+// the return value is the pivot row.  Every lane takes the reciprocal of its own
+// entry while the search runs, so that only a lane read of the pivot's follows
+// it.
+template <int S, int E, typename LT>
+__device__ __forceinline__ int panel_step(LT (&a)[4], LT &q, int row, int k, int &piv, LT &dinv,
+                                          int &info) {
+  const Grp<1> W(0);
+  constexpr uint64_t kLanes = S <= 32 ? 0xffffffffull : ~0ull;  // lanes of the matrix rows
+  int p;
+  bool zero_pivot;
+  LT rown;
+  if constexpr (sizeof(LT) == 4) {
+    const uint32_t key = piv < 0 ? static_cast<uint32_t>(abs_key(a[E])) : 0u;
+    rown = rcp(a[E]);
+    const uint32_t kmax = W.template max_u32<(S + 15) / 16>(key);
+    p = static_cast<int>(__builtin_ctzll(__ballot(key == kmax)));
+    zero_pivot = kmax <= 1u;
+  } else {
+    // high words first (one more than the magnitude's, 0 on used rows), then
+    // the low words of the rows that tie on them
+    const uint64_t bits = __builtin_bit_cast(uint64_t, a[E]);
+    const uint32_t hi = piv < 0 ? (static_cast<uint32_t>(bits >> 32) & 0x7fffffffu) + 1u : 0u;
+    // the search's rounds and the refinement of the reciprocal (rcp()), turn
+    // by turn: a wave issues in order, and either chain alone waits
+    const LT x = a[E];
+    uint32_t v = hi;
+    LT r = __builtin_amdgcn_rcp(x), u;
+    auto up = [](uint32_t c, uint32_t d) { return c > d ? c : d; };
+    v = up(v, __builtin_amdgcn_update_dpp(0u, v, kQuadXor1, 0xf, 0xf, false));
+    asm volatile("" : "+v"(v), "+v"(r));
+    v = up(v, __builtin_amdgcn_update_dpp(0u, v, kQuadXor2, 0xf, 0xf, false));
+    u = fma(-x, r, 1.0);
+    asm volatile("" : "+v"(v), "+v"(u));
+    v = up(v, __builtin_amdgcn_update_dpp(0u, v, kHalfMirror, 0xf, 0xf, false));
+    r = fma(r, u, r);
+    asm volatile("" : "+v"(v), "+v"(r));
+    v = up(v, __builtin_amdgcn_update_dpp(0u, v, kMirror, 0xf, 0xf, false));
+    u = fma(-x, r, 1.0);
+    asm volatile("" : "+v"(v), "+v"(u));
+    v = up(v, __builtin_amdgcn_update_dpp(0u, v, kBcast15, 0xa, 0xf, false));
+    r = fma(r, u, r);
+    asm volatile("" : "+v"(v), "+v"(r));
+    if constexpr (S > 32) v = up(v, __builtin_amdgcn_update_dpp(0u, v, kBcast31, 0xc, 0xf, false));
+    rown = r;
+    const uint32_t hmax = __builtin_amdgcn_readlane(v, S > 32 ? 63 : 31);
+    const uint64_t tie = __ballot(hi == hmax) & kLanes;
+    p = static_cast<int>(__builtin_ctzll(tie | (1ull << 63)));
+    zero_pivot = false;
+    if (__builtin_expect(__builtin_popcountll(tie) != 1, 0)) {
+      const uint32_t lo = static_cast<uint32_t>(bits);
+      const uint32_t lmax = W.template max_u32<(S + 15) / 16>(hi == hmax ? lo : 0u);
+      p = static_cast<int>(__builtin_ctzll(__ballot(hi == hmax && lo == lmax) | (1ull << 63)));
+      zero_pivot = hmax == 1u && lmax == 0u;
     }
-    // lane r takes row r from the lane whose pivot step put it there
-    const int src = W.lane < S ? perm[W.lane] : W.lane;
+  }
+  if (zero_pivot && info == 0) info = k + 1;
+  const bool is_p = row == p;
+  const LT rp = lane_bcast(rown, p);
+  const LT ng = is_p ? static_cast<LT>(0) : -(a[E] * rp);
+  piv = is_p ? k : piv;
+  dinv = is_p ? rown : dinv;
 #pragma unroll
-    for (int t = 0; t < T; ++t) tail->v[t] = lane_pull(a[S - T + t] * dinv, src);
+  for (int j = 1; j < 4; ++j)
+    a[(E + j) & 3] = fma(ng, lane_bcast(a[(E + j) & 3], p), a[(E + j) & 3]);
+  a[E] = is_p ? static_cast<LT>(1) : ng;
+  q = ng;
+  return p;
+}
+
+// One block of the elimination: columns k0 .. k0 + 3 (register t of tile row T),
+// those below n.  The four steps run on the block's own columns; the other
+// columns then take all four rank-1 updates in one matrix product per tile, a
+// chain of four fused multiply-adds per entry in step order, which is the
+// arithmetic of a row-by-row elimination, bit for bit.  The pivot rows they
+// multiply are read through LDS (`scr`, 64 NT entries) one column per lane and
+// brought up to their own step (row p_1 by step 0, p_2 by steps 0 and 1, ...).
+// (A wave issues nothing else while a matrix product runs on this hardware, so
+// there is no point in spreading them.)
+template <int S, int T, int t, typename LT>
+__device__ __forceinline__ void mx_block(TileMat<S, LT> &m, const Grp<1> &W, LT *scr, int n, int k0,
+                                         int &piv, LT &dinv, int &info) {
+  constexpr int NT = TileMat<S, LT>::NT;
+  const int li = W.lane, j = li & 15, g = li >> 4;
+  const bool low = li < 32;
+  const int row = NT == 2 ? li & 31 : li;
+  LT r[NT], a[4], q[4] = {0, 0, 0, 0};
+  int p[4] = {-1, -1, -1, -1};
+#pragma unroll
+  for (int C = 0; C < NT; ++C) r[C] = m.x[T][C][t];
+  to_rows<NT>(r, a);
+  p[0] = panel_step<S, 0>(a, q[0], row, k0, piv, dinv, info);
+  if (k0 + 1 < n) p[1] = panel_step<S, 1>(a, q[1], row, k0 + 1, piv, dinv, info);
+  if (k0 + 2 < n) p[2] = panel_step<S, 2>(a, q[2], row, k0 + 2, piv, dinv, info);
+  if (k0 + 3 < n) p[3] = panel_step<S, 3>(a, q[3], row, k0 + 3, piv, dinv, info);
+  // the pivot rows, entry (k, column c) at (4 k + c % 4) * 4 NT + c / 4
+  typedef LT V2 __attribute__((ext_vector_type(16 / sizeof(LT))));
+  constexpr int VN = 16 / sizeof(LT);
+  wave_lds_sync();
+  // (piv of a row that became a pivot in this block is k0 + its step)
+#pragma unroll
+  for (int C = 0; C < NT; ++C) {
+    const uint32_t k = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute((16 * C + j) << 2, piv) - k0);
+    if (k < 4u && static_cast<int>(k) + k0 < n) {
+      LT *d = scr + (4 * k + g) * (4 * NT);
+#pragma unroll
+      for (int U = 0; U < NT; ++U)
+#pragma unroll
+        for (int u = 0; u < 4; u += VN) {
+          V2 v;
+#pragma unroll
+          for (int w = 0; w < VN; ++w) v[w] = m.x[U][C][u + w];
+          *reinterpret_cast<V2 *>(d + 4 * U + u) = v;
+        }
+    }
+  }
+  wave_lds_sync();
+  LT b[4];
+  {
+    const int c = (row & ~15) + Mx<LT>::col(j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const LT v = scr[(4 * k + (c & 3)) * (4 * NT) + (c >> 2)];
+      b[k] = k0 + k < n ? v : static_cast<LT>(0);
+    }
+  }
+#pragma unroll
+  for (int k = 1; k < 4; ++k)
+#pragma unroll
+    for (int u = 0; u < k; ++u) b[k] = fma(lane_bcast(q[u], p[k]), b[u], b[k]);
+  LT A[NT], B[NT];
+  to_tiles<NT>(q, B, low);
+  to_tiles<NT>(b, A, low);
+#pragma unroll
+  for (int U = 0; U < NT; ++U)
+#pragma unroll
+    for (int C = 0; C < NT; ++C) m.x[U][C] = Mx<LT>::mma(A[U], B[C], m.x[U][C]);
+  // the block's own columns
+  to_tiles<NT>(a, r, low);
+#pragma unroll
+  for (int C = 0; C < NT; ++C) m.x[T][C][t] = r[C];
+}
+
+// Blocks of tile row T, columns k0 .. k0 + 15, those below n.
+template <int S, int T, typename LT>
+__device__ __forceinline__ void mx_tile_row(TileMat<S, LT> &m, const Grp<1> &W, LT *scr, int n, int k0,
+                                            int &piv, LT &dinv, int &info) {
+  if (k0 < n) mx_block<S, T, 0>(m, W, scr, n, k0, piv, dinv, info);
+  if (k0 + 4 < n) mx_block<S, T, 1>(m, W, scr, n, k0 + 4, piv, dinv, info);
+  if (k0 + 8 < n) mx_block<S, T, 2>(m, W, scr, n, k0 + 8, piv, dinv, info);
+  if (k0 + 12 < n) mx_block<S, T, 3>(m, W, scr, n, k0 + 12, piv, dinv, info);
+}
+
+// Inverts the cell's Newton matrix held in tiles; results as invert() of a
+// RowMat (same pivots, same arithmetic).  The first n rows and columns are
+// eliminated; the padding beyond them is an identity, whose elimination changes
+// nothing.
+template <int S, typename LT, int T = 0>
+__device__ __forceinline__ int invert(TileMat<S, LT> &m, const Grp<1> &W, const Lds &L, int n,
+                                      InvTail<T, LT> *tail = nullptr) {
+  constexpr int NT = TileMat<S, LT>::NT;
+  const Grp<1> V = local_lane(W);
+  const int li = V.lane, j = li & 15, g = li >> 4;
+  const int row = NT == 2 ? li & 31 : li;
+  int piv = row < n ? -1 : row;
+  int info = 0;
+  LT dinv = static_cast<LT>(1);  // 1 / own pivot
+  // the matrix area, from its first 16-byte boundary (an index, not a rounded
+  // address: the pointer stays an LDS pointer)
+  LT *scr = reinterpret_cast<LT *>(reinterpret_cast<double *>(L.fac) +
+                                   ((reinterpret_cast<uintptr_t>(L.fac) >> 3) & 1));
+  if constexpr (NT == 2) {
+    mx_tile_row<S, 0>(m, V, scr, n, 0, piv, dinv, info);
+    mx_tile_row<S, 1>(m, V, scr, n, 16, piv, dinv, info);
+  } else {
+    // one copy of the code (the instruction cache): the tile rows move up by
+    // one after each pass
+#pragma unroll 1
+    for (int k0 = 0; k0 < 64; k0 += 16) {
+      mx_tile_row<S, 0>(m, V, scr, n, k0, piv, dinv, info);
+#pragma unroll
+      for (int C = 0; C < NT; ++C) {
+        const typename Mx<LT>::V first = m.x[0][C];
+#pragma unroll
+        for (int U = 0; U + 1 < NT; ++U) m.x[U][C] = m.x[U + 1][C];
+        m.x[NT - 1][C] = first;
+      }
+    }
+  }
+  // row i became row piv(i) of M^{-1} (times its pivot); slot k is column perm[k]
+  int *perm = L.perm;
+  LT *inv = reinterpret_cast<LT *>(L.fac);
+  LT *dv = reinterpret_cast<LT *>(L.yb);
+  int *pv = reinterpret_cast<int *>(L.fb);
+  wave_lds_sync();
+  if (li < S) {
+    perm[piv] = li;
+    dv[li] = dinv;
+    pv[li] = piv;
+  }
+  wave_lds_sync();
+  LT d[NT];
+  int to[NT];
+#pragma unroll
+  for (int C = 0; C < NT; ++C) {
+    const int i = 16 * C + j < S ? 16 * C + j : 0;
+    d[C] = dv[i];
+    to[C] = pv[i];
+  }
+  if constexpr (T > 0) {
+    // the last T slots first, through the area they will not stay in
+#pragma unroll
+    for (int u = S - T; u < S + 3; u += 4) {
+      const int col = u + g;
+      if (col < S) {
+#pragma unroll
+        for (int C = 0; C < NT; ++C)
+          if (16 * C + j < S) inv[(col - (S - T)) * S + to[C]] = m.x[u / 16][C][u / 4 % 4] * d[C];
+      }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < T; ++u) tail->v[u] = inv[u * S + (li < S ? li : 0)];
+    wave_lds_sync();
+  }
+  static_assert((S - T) % 4 == 0 || T == 0, "whole groups of four columns in LDS");
+  const LT *cbase[4 * NT];  // T == 0: the inverse column of each of the lane's slots
+  if constexpr (T == 0) {
+#pragma unroll
+    for (int q = 0; 4 * q < S; ++q) cbase[q] = inv + perm[4 * q + g < S ? 4 * q + g : 0] * S;
+  }
+#pragma unroll
+  for (int C = 0; C < NT; ++C) {
+    if (16 * C >= S) continue;
+    if (16 * C + 15 < S || 16 * C + j < S) {
+#pragma unroll
+      for (int q = 0; 4 * q < S - T; ++q) {
+        const LT v = m.x[q / 4][C][q % 4] * d[C];
+        if constexpr (T > 0) {
+          inv[(4 * q + g) * S + to[C]] = v;
+        } else {
+          if (4 * q + 3 < S || 4 * q + g < S) const_cast<LT *>(cbase[q])[to[C]] = v;
+        }
+      }
+    }
   }
   wave_lds_sync();
   return info;
@@ -1221,26 +1752,47 @@ __device__ __forceinline__ int gj_invert(LT (&a)[S], const Grp<G> &W, const Lds 
 template <int S, typename LT, bool SPLIT, int T = 0, int G>
 __device__ __forceinline__ double inv_solve(const Lds &L, const Grp<G> &W, double b,
                                             const InvTail<T, LT> *tail = nullptr) {
+  const Grp<G> V = local_lane(W);
   const LT *inv = reinterpret_cast<const LT *>(L.fac);
   LT *bb = reinterpret_cast<LT *>(L.yb);
   if constexpr (T > 0) {
     static_assert(!SPLIT && sizeof(LT) == 8, "an inverse tail: FP64, one chain");
     wave_lds_sync();
-    const double bk = lane_pull(b, W.lane < S ? L.perm[W.lane] : W.lane);
-    if (W.lane < S) bb[W.lane] = bk;
+    const double bk = lane_pull(b, V.lane < S ? L.perm[V.lane] : V.lane);
+    if (V.lane < S) bb[V.lane] = bk;
     wave_lds_sync();
-    const int lr = W.lane < S ? W.lane : 0;
+    const int lr = V.lane < S ? V.lane : 0;
     LT acc = 0;
+    // one chain of additions (its order is part of the result); the loads of
+    // NB slots are issued ahead of the NB before them
+    constexpr int NB = 11, N = (S - T) / NB;
+    static_assert(N * NB == S - T, "whole blocks of slots");
+    LT v[2][NB], x[2][NB];
 #pragma unroll
-    for (int k = 0; k < S - T; ++k) acc = fma(inv[k * S + lr], bb[k], acc);
+    for (int u = 0; u < NB; ++u) {
+      v[0][u] = inv[u * S + lr];
+      x[0][u] = bb[u];
+    }
 #pragma unroll
-    for (int t = 0; t < T; ++t) acc = fma(tail->v[t], bb[S - T + t], acc);
-    return W.lane < S ? static_cast<double>(acc) : 0.0;
+    for (int k = 0; k < N; ++k) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        if (k + 1 < N) v[(k + 1) & 1][u] = inv[((k + 1) * NB + u) * S + lr];
+        if (k + 1 < N || u < T) x[(k + 1) & 1][u] = bb[(k + 1) * NB + u];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) acc = fma(v[k & 1][u], x[k & 1][u], acc);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc = fma(tail->v[t], x[N & 1][t], acc);
+    return V.lane < S ? static_cast<double>(acc) : 0.0;
   }
   wave_lds_sync();
-  if (W.lane < S) bb[W.lane] = static_cast<LT>(b);
+  if (V.lane < S) bb[V.lane] = static_cast<LT>(b);
   wave_lds_sync();
-  const int lr = W.lane < S ? W.lane : 0;
+  const int lr = V.lane < S ? V.lane : 0;
   if constexpr (SPLIT) {
     // three partial sums (column c into sum c mod 3, added in a fixed order)
     // shorten the dependent FMA chain, and the unrolled loop issues the LDS
@@ -1254,12 +1806,12 @@ __device__ __forceinline__ double inv_solve(const Lds &L, const Grp<G> &W, doubl
       if (c + 1 < S) acc1 = fma(inv[(c + 1) * S + lr], bb[c + 1], acc1);
       if (c + 2 < S) acc2 = fma(inv[(c + 2) * S + lr], bb[c + 2], acc2);
     }
-    return W.lane < S ? static_cast<double>((acc0 + acc1) + acc2) : 0.0;
+    return V.lane < S ? static_cast<double>((acc0 + acc1) + acc2) : 0.0;
   } else {
     LT acc = 0;
 #pragma unroll
     for (int c = 0; c < S; ++c) acc = fma(inv[c * S + lr], bb[c], acc);
-    return W.lane < S ? static_cast<double>(acc) : 0.0;
+    return V.lane < S ? static_cast<double>(acc) : 0.0;
   }
 }
 
@@ -1430,6 +1982,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
   static_assert(!RES || (G == 1 && !LOCK && !TH && LIN == kLinAnalytic && sizeof(LT) == 8),
                 "resumed integrations: FP64 direct solver, analytic Jacobian, one cell per wave");
   constexpr bool KRY = LIN == kLinGmres;
+  constexpr int NP = TAB == kTabGlobal ? 6 : 2;  // reaction passes loaded ahead
   const MechDev &m = P.mech;
   const int R = m.R;
   const int ns = m.S;  // species; a non-isothermal state also holds T at entry ns
@@ -1520,9 +2073,9 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
     if (!need_setup) {
       // the inverse the run held: the same matrix at the same state and gamma
       const double zs = own ? ck[Ckpt::vec(Ckpt::kVecSetup, S) + W.lane] : 0.0;
-      LT a[S];
+      Mat<S, LT, G> a;
       newton_matrix<S, LT, ABC, TL>(a, m, L, W, zs, uni(ck[Ckpt::kGammaBar]), false);
-      gj_invert<S, LT, TL>(a, W, L, &itail);
+      invert<S, LT, TL>(a, W, L, n, &itail);
     }
   } else {
     const double yin = own ? P.y[cell * P.ldy + W.lane] : 0.0;
@@ -1533,7 +2086,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
     }
     if (status == kSuccess) {
       z[0] = yin;
-      f = rhs<ABC, TH>(m, L, W, yin, Fi, ns);
+      f = rhs<ABC, TH, NP>(m, L, W, yin, Fi, ns);
       nfe = 1;
       if (br.any(W.any(own && !isfinite(f)))) {
         status = kNonfinite;
@@ -1555,7 +2108,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
         double hg = sqrt(hlb * hub), hnew = hg;
         bool at_ub = false;
         for (int it = 0; it < 4; ++it) {
-          const double ft = rhs<ABC, TH>(m, L, W, yin + hg * f, Fi, ns);
+          const double ft = rhs<ABC, TH, NP>(m, L, W, yin + hg * f, Fi, ns);
           nfe++;
           const double ydd = (ft - f) / hg;
           const double yddnrm = sqrt(norm2(ydd, ewt));
@@ -1639,7 +2192,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
     double dsm2 = 0.0, Cerr = 0.5;
     for (;;) {  // attempts of this step
       bool landing = false;
-      if (t + h >= tout * (1.0 - 4.0 * kUround)) {
+      if (plain_sum(t, h) >= tout * (1.0 - 4.0 * kUround)) {
         const double hnew = W.uni(tout - t);
         nd_rescale(z, hnew / h);
         h = hnew;
@@ -1651,29 +2204,8 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       }
       nd_predict(z);
       double l1;
-      {
-        // xi_i = (t_n - t_{n-i}) / h and the coefficients of this attempt
-        double xi[kQmax + 2], l[kQmax + 2];
-        double sum = h;
-        const double rh = rcp(h);
-        xi[0] = 0.0;
-        xi[1] = 1.0;
-#pragma unroll
-        for (int i = 2; i <= kQmax + 1; ++i) {
-          sum += C[Ctl::kHist + i - 2];
-          xi[i] = i <= q + 1 ? sum * rh : 0.0;
-        }
-        bdf_coeffs(q, xi, l, Cerr);
-        wave_lds_sync();
-#pragma unroll
-        for (int i = 0; i <= kQmax + 1; ++i) {
-          C[Ctl::kXi + i] = xi[i];
-          C[Ctl::kL + i] = l[i];
-        }
-        C[Ctl::kTn] = landing ? tout : t + h;
-        l1 = W.uni(l[1]);
-        Cerr = W.uni(Cerr);
-      }
+      step_coeffs(q, h, C, C + Ctl::kHist, Ctl::kXi, Ctl::kL, W, l1, Cerr);
+      C[Ctl::kTn] = landing ? tout : plain_sum(t, h);
       const double rl1 = W.uni(rcp(l1));
       const double gamma = W.uni(h * rl1);
       double gamma_bar = W.uni(C[Ctl::kGammaBar]);
@@ -1681,10 +2213,14 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       // (gamma_bar = 0 before the first setup, which need_setup forces)
       // (GMRES kernels form no matrix and take no setups)
       if constexpr (!KRY) {
-        if (need_setup || nst >= nst_setup + 20 || fabs(gamma * rcp(gamma_bar) - 1.0) > 0.3) {
+        // (unlikely, every eighth step: spills belong into this branch, whose
+        // elimination needs the most registers)
+        if (__builtin_expect(need_setup || nst >= nst_setup + 20 ||
+                                 fabs(gamma * rcp(gamma_bar) - 1.0) > 0.3,
+                             0)) {
           int info;
           {
-            LT a[S];
+            Mat<S, LT, G> a;
             if constexpr (LIN == kLinDq) {
               dq_matrix<S, LT, ABC, TH>(a, m, L, W, z[0], Fi, gamma, h, ewt, ns, n, inv_n);
               nfe += n + 1;
@@ -1693,7 +2229,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
             } else {
               newton_matrix<S, LT, ABC, TL>(a, m, L, W, z[0], gamma, false);
             }
-            info = gj_invert<S, LT, TL>(a, W, L, &itail);
+            info = invert<S, LT, TL>(a, W, L, n, &itail);
           }
           if (!RES && P.ckpt && own) P.ckpt_setup[cell * P.ckpt_vs + W.lane] = z[0];
           nsetups++;
@@ -1727,12 +2263,12 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
 
       // Newton iteration on G(e) = e - gamma f(z_0 + e) + z_1 / l_1, Eq. (4)
       bool conv = false;
-      double dprev2 = 0.0;
+      double dprev2 = 0.0, en2 = 0.0;
       // stopping test of Eq. (4) with eps = 1/Cerr, on squared norms
       const double tol2 = 0.01 * W.uni(rcp(Cerr * Cerr));
       e = 0.0;
       for (int mit = 0; mit < 3; ++mit) {
-        f = rhs<ABC, TH>(m, L, W, z[0] + e, Fi, ns);
+        f = rhs<ABC, TH, NP>(m, L, W, z[0] + e, Fi, ns);
         nfe++;
         nni++;
         const double Gi = e - gamma * f + z[1] * rl1;
@@ -1751,7 +2287,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
           delta = inv_solve<S, LT, sizeof(LT) == 4 && !TH, TL>(L, W, -Gi, &itail);
           if (cfac != 1.0) delta *= cfac;
         }
-        e += delta;
+        e = plain_sum(e, delta);
         const double d2 = norm2(delta, ewt);
         if (!isfinite(d2)) break;
         if (mit >= 1) {
@@ -1760,6 +2296,8 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
         }
         if ((R2 < 1.0 ? R2 : 1.0) * d2 <= tol2) {
           conv = true;
+          // the squared norm of e, which is delta after one iteration
+          en2 = mit == 0 ? d2 : norm2(e, ewt);
           break;
         }
         if (mit >= 1 && d2 > 4.0 * dprev2) break;
@@ -1782,7 +2320,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       }
 
       // local error test (Sec. 2)
-      dsm2 = W.uni(Cerr * Cerr * norm2(e, ewt));
+      dsm2 = W.uni(Cerr * Cerr * en2);
       if (dsm2 <= 1.0) break;
       netf++;
       nd_unpredict(z);
@@ -1795,7 +2333,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
         // restart at order 1 from the last accepted y
         const double hnew = W.uni(0.1 * h);
         q = 1;
-        const double f0 = rhs<ABC, TH>(m, L, W, z[0], Fi, ns);
+        const double f0 = rhs<ABC, TH, NP>(m, L, W, z[0], Fi, ns);
         nfe++;
 #pragma unroll
         for (int j = 2; j <= kQmax; ++j) z[j] = 0.0;
@@ -1981,7 +2519,7 @@ __device__ __forceinline__ double adj_scatter(const MechDev &m, const Lds &L, do
   vb[li] = vi;
   L.fb[li] = 0.0;
   wave_lds_sync();
-  for (int r = li; r < m.R; r += kWave) {
+  auto scatter = [&](int r) {
     const int2 w = L.rx[r];
     int a[3], b[3];
     double pf = L.kk[2 * r], pr = L.kk[2 * r + 1], s = 0.0;
@@ -2016,6 +2554,10 @@ __device__ __forceinline__ double adj_scatter(const MechDev &m, const Lds &L, do
         }
       }
     }
+  };
+  for (int r0 = 0; r0 < m.R; r0 += kWave) {
+    if (r0 + li < m.R) scatter(r0 + li);
+    lanes_meet();
   }
   wave_lds_sync();
   return L.fb[li];
@@ -2114,9 +2656,9 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
     zb[0] -= eb;
     // (I - gamma J(y_n))^T mu = eb
     {
-      double a[S];
+      Mat<S, double, 1> a;
       newton_matrix<S, double>(a, m, L, W1, yn, gamma, true);
-      gj_invert<S, double>(a, W1, L);
+      invert<S, double>(a, W1, L, n);
     }
     const double mu = own ? inv_solve<S, double, false>(L, W1, eb) : 0.0;
     adj_scatter(m, L, vb, pb, li, yn, mu, gamma, false);

@@ -31,7 +31,9 @@ template <int S, typename LT, int MINW, int TAB, int G, bool ABC, bool TH,
           int LIN = kLinAnalytic, bool LOCK = false>
 __global__ void __launch_bounds__(LOCK ? kWave * kMaxBatch : 256, MINW) k_integrate(Params P) {
   extern __shared__ double smem[];
-  const int wib = threadIdx.x / kWave;
+  // (a scalar LDS base; the non-isothermal kernels keep the form in which their
+  // energy sums are fused as they always were: with it the last bits moved)
+  const int wib = TH ? static_cast<int>(threadIdx.x / kWave) : uni(static_cast<int>(threadIdx.x / kWave));
   const Grp<G> W(threadIdx.x & (kWave - 1));
   const int wpb = blockDim.x / kWave;
   double *lds = smem + static_cast<int64_t>(wib * G + W.grp) * P.lds_doubles;
@@ -64,8 +66,10 @@ __global__ void __launch_bounds__(LOCK ? kWave * kMaxBatch : 256, MINW) k_integr
     return;
   }
   double *kk_slot = nullptr;
+  static_assert(TAB != kTabGlobal || G == 1, "rate-constant slots: one cell per wave");
   if constexpr (TAB == kTabGlobal)
-    kk_slot = P.kk_slots + ((static_cast<int64_t>(blockIdx.x) * wpb + wib) * G + W.grp) * (2 * P.mech.R);
+    // (one address for the wave, in scalar registers; G = 1)
+    kk_slot = P.kk_slots + (static_cast<int64_t>(blockIdx.x) * wpb + uni(wib)) * (2 * P.mech.R);
   int64_t next = 0, stop = 0;
   if (!P.use_queue) {
     next = (static_cast<int64_t>(blockIdx.x) * wpb + wib) * G + W.grp;
@@ -100,7 +104,7 @@ __global__ void __launch_bounds__(LOCK ? kWave * kMaxBatch : 256, MINW) k_integr
 template <int SA, int SB, typename LT, int MINW, int TABA>
 __global__ void __launch_bounds__(256, MINW) k_integrate_pair(Params PA, Params PB) {
   extern __shared__ double smem[];
-  const int wib = threadIdx.x / kWave;
+  const int wib = uni(static_cast<int>(threadIdx.x / kWave));
   const Grp<1> W(threadIdx.x & (kWave - 1));
   const int wa = PA.pair_waves;
   const bool is_a = wib < wa;
@@ -109,7 +113,7 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_pair(Params PA, Params 
                            static_cast<int64_t>(wib - wa) * PB.lds_doubles;
   double *kk_slot = nullptr;
   if constexpr (TABA == kTabGlobal)
-    if (is_a) kk_slot = PA.kk_slots + (static_cast<int64_t>(blockIdx.x) * wa + wib) * (2 * PA.mech.R);
+    if (is_a) kk_slot = PA.kk_slots + (static_cast<int64_t>(blockIdx.x) * wa + uni(wib)) * (2 * PA.mech.R);
   int64_t next = 0, stop = 0;
   if (is_a) {
     for (;;) {
@@ -144,30 +148,26 @@ template <int SA, int SB>
 const void *pair_kernel(bool fp32, int minw, int taba) {
   using F = const void *;
   if (minw >= 5) return nullptr;  // built for the budgets 0, 3 and 4
-  const int w = minw >= 4 ? 2 : minw >= 3 ? 1 : 0;
-  static const F t64[3][3] = {
-      {F(&k_integrate_pair<SA, SB, double, 1, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, double, 1, kTabLds>),
-       F(&k_integrate_pair<SA, SB, double, 1, kTabGlobal>)},
-      {F(&k_integrate_pair<SA, SB, double, 3, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, double, 3, kTabLds>),
-       F(&k_integrate_pair<SA, SB, double, 3, kTabGlobal>)},
-      {F(&k_integrate_pair<SA, SB, double, 4, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, double, 4, kTabLds>),
-       F(&k_integrate_pair<SA, SB, double, 4, kTabGlobal>)}};
-  static const F t32[3][3] = {
-      {F(&k_integrate_pair<SA, SB, float, 1, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, float, 1, kTabLds>),
-       F(&k_integrate_pair<SA, SB, float, 1, kTabGlobal>)},
+  // one register budget per precision: the larger mechanism's (see by_budget)
+  static const F t[2][3] = {
+      {F(&k_integrate_pair<SA, SB, double, 2, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, double, 2, kTabLds>),
+       F(&k_integrate_pair<SA, SB, double, 2, kTabGlobal>)},
       {F(&k_integrate_pair<SA, SB, float, 3, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, float, 3, kTabLds>),
-       F(&k_integrate_pair<SA, SB, float, 3, kTabGlobal>)},
-      {F(&k_integrate_pair<SA, SB, float, 4, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, float, 4, kTabLds>),
-       F(&k_integrate_pair<SA, SB, float, 4, kTabGlobal>)}};
+       F(&k_integrate_pair<SA, SB, float, 3, kTabGlobal>)}};
   if (taba < 0 || taba > 2) return nullptr;
-  return fp32 ? t32[w][taba] : t64[w][taba];
+  return t[fp32 ? 1 : 0][taba];
 }
 
 // Adjoint sweep over a full record: one wave per cell.
+// Waves per SIMD the adjoint kernels' registers must allow (1: compiler's
+// choice).  At 21 species the tiled elimination takes 100 to 110 registers, so
+// four; without a bound it took 153.
+__host__ __device__ constexpr int adjoint_waves(int S) { return S > 32 ? 2 : S > 16 ? 4 : 1; }
+
 template <int S>
-__global__ void __launch_bounds__(256) k_adjoint(Params P) {
+__global__ void __launch_bounds__(256, adjoint_waves(S)) k_adjoint(Params P) {
   extern __shared__ double smem[];
-  const int wib = threadIdx.x / kWave;
+  const int wib = uni(static_cast<int>(threadIdx.x / kWave));
   const int li = threadIdx.x & (kWave - 1);
   const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wib;
   if (w >= P.n_list) return;
@@ -184,9 +184,9 @@ __global__ void __launch_bounds__(256) k_adjoint(Params P) {
 // once.  (A persistent loop over cells costs these kernels 20-35 % more
 // registers.)  ABC as in k_integrate.
 template <int S, bool ABC>
-__global__ void __launch_bounds__(256) k_adj_rerun(Params P, int j) {
+__global__ void __launch_bounds__(256, adjoint_waves(S)) k_adj_rerun(Params P, int j) {
   extern __shared__ double smem[];
-  const int wib = threadIdx.x / kWave;
+  const int wib = uni(static_cast<int>(threadIdx.x / kWave));
   const Grp<1> W(threadIdx.x & (kWave - 1));
   const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wib;
   if (w >= P.n_list) return;
@@ -194,9 +194,9 @@ __global__ void __launch_bounds__(256) k_adj_rerun(Params P, int j) {
 }
 
 template <int S>
-__global__ void __launch_bounds__(256) k_adj_sweep(Params P, int j) {
+__global__ void __launch_bounds__(256, adjoint_waves(S)) k_adj_sweep(Params P, int j) {
   extern __shared__ double smem[];
-  const int wib = threadIdx.x / kWave;
+  const int wib = uni(static_cast<int>(threadIdx.x / kWave));
   const int li = threadIdx.x & (kWave - 1);
   const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wib;
   if (w >= P.n_list) return;
@@ -210,11 +210,6 @@ const void *adjoint_kernel(int kind, bool abc) {
   if (kind == 2) return (const void *)&k_adj_sweep<S>;
   return abc ? (const void *)&k_adj_rerun<S, true> : (const void *)&k_adj_rerun<S, false>;
 }
-
-struct LaunchCfg {
-  int grid, block;
-  size_t lds_bytes;
-};
 
 // the three register budgets of one kernel configuration
 // lock-step kernels: one register budget (the block of up to 16 waves caps
@@ -231,10 +226,20 @@ const void *lock_kernel(bool fp32, bool abc) {
 template <int S, typename LT, int TAB, int G, bool ABC, bool TH = false, int LIN = kLinAnalytic>
 const void *by_budget(int w) {
   using F = const void *;
-  static const F t[4] = {F(&k_integrate<S, LT, 1, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, 3, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, 4, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, 5, TAB, G, ABC, TH, LIN>)};
+  // The tiled elimination keeps the whole matrix in registers, so above 32
+  // species a budget for more waves than the LDS lets reside (the inverse: two
+  // waves per SIMD in FP64, three in FP32) only spills it: 53 species FP64 at
+  // the 3-wave budget took 44 ms on 4,096 cells against 25.
+  constexpr bool kBig = S > 32 && LIN != kLinGmres;
+  constexpr int CAP = kBig ? (sizeof(LT) == 8 ? 2 : 3) : 5;
+  // budget 0, the compiler's choice: bounded where the elimination would take
+  // more registers than leave the waves the LDS has room for
+  constexpr int W0 = kBig ? CAP : S > 16 && LIN != kLinGmres ? 3 : 1;
+  constexpr int W3 = CAP < 3 ? CAP : 3, W4 = CAP < 4 ? CAP : 4, W5 = CAP;
+  static const F t[4] = {F(&k_integrate<S, LT, W0, TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, W3, TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, W4, TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, W5, TAB, G, ABC, TH, LIN>)};
   return t[w];
 }
 
