@@ -19,6 +19,7 @@
 
 #include "bdfx.h"
 #include "bdf_kernels.h"
+#include "bdf_packed.h"
 
 BDFX_DECLARE_SIZE(3)
 BDFX_DECLARE_SIZE(4)
@@ -30,6 +31,12 @@ BDFX_DECLARE_SIZE(32)
 BDFX_DECLARE_SIZE(53)
 BDFX_DECLARE_SIZE(64)
 BDFX_DECLARE_PAIR(53, 9)
+BDFX_DECLARE_PACKED(3)
+BDFX_DECLARE_PACKED(4)
+BDFX_DECLARE_PACKED(8)
+BDFX_DECLARE_PACKED(9)
+BDFX_DECLARE_PACKED(16)
+BDFX_DECLARE_PACKED(21)
 
 hipError_t bdfx_launch_perturb(const bdfx::Params &P, uint64_t seed, int64_t step, double amp,
                                hipStream_t s);
@@ -60,17 +67,23 @@ struct SizeEntry {
   // adjoint kernels (kind 0: full-record sweep; 1, 2: rerun and sweep of a
   // checkpointed pass)
   hipError_t (*adjoint)(const bdfx::Params &, int, int, bool, const bdfx::LaunchCfg &, hipStream_t);
-
+  // several cells per wave (nullptr: the mechanism fills the wave)
+  hipError_t (*launch_packed)(const bdfx::Params &, bool, bool, const bdfx::LaunchCfg &, hipStream_t);
+  hipError_t (*occupancy_packed)(bool, bool, int, size_t, int *);
 };
 
 #define BDFX_SIZE_ENTRY(S) \
-  {S, bdfx_launch_s##S, bdfx_occupancy_s##S, bdfx_adjoint_s##S}
+  {S, bdfx_launch_s##S, bdfx_occupancy_s##S, bdfx_adjoint_s##S, nullptr, nullptr}
+#define BDFX_SIZE_ENTRY_PACKED(S)                                                                  \
+  {S, bdfx_launch_s##S, bdfx_occupancy_s##S, bdfx_adjoint_s##S, bdfx_launch_packed_s##S,           \
+   bdfx_occupancy_packed_s##S}
 const SizeEntry kSizes[] = {
-    BDFX_SIZE_ENTRY(3),  BDFX_SIZE_ENTRY(4),  BDFX_SIZE_ENTRY(8),
-    BDFX_SIZE_ENTRY(9),  BDFX_SIZE_ENTRY(16), BDFX_SIZE_ENTRY(21),
-    BDFX_SIZE_ENTRY(32), BDFX_SIZE_ENTRY(53), BDFX_SIZE_ENTRY(64),
+    BDFX_SIZE_ENTRY_PACKED(3),  BDFX_SIZE_ENTRY_PACKED(4),  BDFX_SIZE_ENTRY_PACKED(8),
+    BDFX_SIZE_ENTRY_PACKED(9),  BDFX_SIZE_ENTRY_PACKED(16), BDFX_SIZE_ENTRY_PACKED(21),
+    BDFX_SIZE_ENTRY(32),        BDFX_SIZE_ENTRY(53),        BDFX_SIZE_ENTRY(64),
 };
 #undef BDFX_SIZE_ENTRY
+#undef BDFX_SIZE_ENTRY_PACKED
 
 // Smallest compiled size that holds S species (exact sizes 3, 9, 21, 53 are
 // compiled for the benchmark mechanisms; others are padded with inert
@@ -133,6 +146,7 @@ struct Bin {
   // launch shape: from the options, or chosen by bdfx_autotune()
   int32_t waves_per_simd = 0, waves_per_block = 1, queue_chunk = 1, cells_per_wave = 1;
   bool tuned = false;
+  int packed = 1;  // cells per wave of the packed kernel in effect (1: k_integrate)
   int tab = bdfx::kTabLds;  // placement of the reaction tables (bdfx::kTab*)
   int64_t tune_sample = 0;  // bdfx_autotune(): cells timed and time of the pick
   float tune_ms = 0.0f;
@@ -591,6 +605,54 @@ int bdfx_bind(bdfx_ctx ctx, void *d_ws, size_t ws_bytes, double *d_y, int32_t ld
 // integrate
 // ---------------------------------------------------------------------------
 
+// Cells per wave of this bin's launch under the library's own choice of shape
+// (waves_per_simd 0, one cell per wave asked for): the packed kernel's count
+// where it applies and the cells are enough for it, else 1.  Results do not
+// depend on it.
+static int packed_cells_of(bdfx_ctx ctx, const Bin &b) {
+  const bdfx_mech m = ctx->mechs[b.mech];
+  if (!b.se->launch_packed || b.cells_per_wave != 1 || b.waves_per_simd != 0 || m->thermal ||
+      lin_of(ctx) != bdfx::kLinAnalytic || ctx->opt.lockstep > 0 || ctx->opt.checkpoint_every > 0 ||
+      b.count < static_cast<int64_t>(bdfx::packed_min_cells_per_cu(b.se->S)) * ctx->n_cu)
+    return 1;
+  return bdfx::packed_cells(b.se->S);
+}
+
+// Launch of the packed kernel: persistent waves, as many as are resident.
+static int configure_packed(bdfx_ctx ctx, Bin &b) {
+  const bool fp32 = ctx->opt.lu_precision == 32;
+  const bdfx_mech m = ctx->mechs[b.mech];
+  const int waves = std::min(std::max(b.waves_per_block, 1), 4);
+  b.cfg.block = bdfx::kWave * waves;
+  b.lds_doubles = b.packed == 4 ? bdfx::PackLds<4>::size(b.se->S, m->R, fp32 ? 4 : 8)
+                                : bdfx::PackLds<2>::size(b.se->S, m->R, fp32 ? 4 : 8);
+  b.cfg.lds_bytes = (static_cast<size_t>(waves) * b.packed * b.lds_doubles +
+                     bdfx::PackHead::size(m->R)) * 8;
+  b.tab = bdfx::kTabLds;
+  int occ = 0;
+  if (b.cfg.lds_bytes <= 65536)
+    HIPCHK(ctx, b.se->occupancy_packed(fp32, m->abc, b.cfg.block, b.cfg.lds_bytes, &occ));
+  if (occ < 1) {  // a mechanism whose areas do not fit: one cell per wave
+    b.packed = 1;
+    return BDFX_OK;
+  }
+  const int per_cu = ctx->opt.blocks_per_cu > 0 ? ctx->opt.blocks_per_cu : occ;
+  const int64_t per_block = static_cast<int64_t>(waves) * b.packed;
+  b.cfg.grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(per_cu) * ctx->n_cu,
+                                                  (b.count + per_block - 1) / per_block));
+  return BDFX_OK;
+}
+
+// Enqueues one bin's integration (P from make_params of the same bin).
+static hipError_t launch_bin(bdfx_ctx ctx, const Bin &b, bdfx::Params P) {
+  const bool fp32 = ctx->opt.lu_precision == 32;
+  const bdfx_mech m = ctx->mechs[b.mech];
+  P.lds_doubles = b.lds_doubles;
+  if (b.packed > 1) return b.se->launch_packed(P, fp32, m->abc, b.cfg, ctx->stream);
+  return b.se->launch(P, fp32, b.waves_per_simd, b.tab, b.cells_per_wave, kernel_flags(ctx, m),
+                      b.cfg, ctx->stream);
+}
+
 // Kernel, LDS size and grid of one bin from its launch shape.
 static int configure_bin(bdfx_ctx ctx, Bin &b) {
   const bool fp32 = ctx->opt.lu_precision == 32;
@@ -605,6 +667,11 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
   // lock-step: one block per batch, one wave per cell of it, tables in LDS,
   // and the batch's reduction slots after the waves' areas
   const int lock = ctx->opt.lockstep;
+  b.packed = packed_cells_of(ctx, b);
+  if (b.packed > 1) {
+    const int rc = configure_packed(ctx, b);
+    if (rc || b.packed > 1) return rc;
+  }
   if (lock > 0) {  // the one shape of the lock-step kernels, as reported by bdfx_get_tuning
     b.waves_per_block = lock;
     b.waves_per_simd = 0;
@@ -835,9 +902,7 @@ int bdfx_integrate(bdfx_ctx ctx, double t0, double t_out) {
     if (b.count == 0 || b.cfg.grid < 1) continue;
     bdfx::Params P = make_params(ctx, b, t0, t_out);
     P.use_queue = queue ? 1 : 0;
-    P.lds_doubles = b.lds_doubles;
-    HIPCHK(ctx, b.se->launch(P, fp32, b.waves_per_simd, b.tab, b.cells_per_wave,
-                             kernel_flags(ctx, ctx->mechs[b.mech]), b.cfg, ctx->stream));
+    HIPCHK(ctx, launch_bin(ctx, b, P));
   }
   ctx->last_t0 = t0;
   ctx->last_tout = t_out;
@@ -914,11 +979,7 @@ static hipError_t time_pair(bdfx_ctx ctx, double t0, double t_out, int64_t ns, h
       if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
       if (e == hipSuccess) e = bdfx_launch_fill_u32(qctr, 64, 0u, ctx->stream);
       if (form == 0) {
-        for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-          const bdfx_mech m = ctx->mechs[tb[k].mech];
-          e = tb[k].se->launch(P[k], fp32, tb[k].waves_per_simd, tb[k].tab, 1, kernel_flags(ctx, m),
-                               tb[k].cfg, ctx->stream);
-        }
+        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = launch_bin(ctx, tb[k], P[k]);
       } else if (e == hipSuccess) {
         bdfx::Params PA = P[0], PB = P[1];
         PB.lds_doubles = ctx->pair_lds_b;
@@ -988,7 +1049,6 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
           trial.waves_per_block = wpb;
           trial.queue_chunk = chunk;
           if (configure_bin(ctx, trial) != BDFX_OK) continue;  // e.g. LDS too large
-          P.lds_doubles = trial.lds_doubles;
           P.chunk = chunk;
           float total = 0.0f;
           hipError_t e = hipSuccess;
@@ -997,9 +1057,7 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
                                       ctx->stream);
             if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
             if (e == hipSuccess && queue) e = bdfx_launch_fill_u32(qctr, 64, 0u, ctx->stream);
-            if (e == hipSuccess)
-              e = trial.se->launch(P, fp32, wps, trial.tab, cpw, kernel_flags(ctx, m), trial.cfg,
-                                   ctx->stream);
+            if (e == hipSuccess) e = launch_bin(ctx, trial, P);
             if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
             if (e == hipSuccess)
               e = bdfx_launch_copy_rows(ctx->y, ctx->ldy, P.list, trial.count, m->n, save, true,

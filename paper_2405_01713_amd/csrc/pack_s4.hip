@@ -1,0 +1,4 @@
+// 4 species, several cells per wave.
+#include "bdf_packed.h"
+
+BDFX_DEFINE_PACKED(4)

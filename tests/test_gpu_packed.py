@@ -1,0 +1,68 @@
+"""Several cells per wave (the library's own launch shape for many cells of a
+small mechanism) against one cell per wave: the same bits, counters included."""
+import numpy as np
+import pytest
+
+from paper_2405_01713_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(w, y0, **opts):
+    import torch
+    from paper_2405_01713_amd import bdfx
+    integ = bdfx.Integrator(w["mechs"], y0, 1e-6, 1e-10, T=w.get("T"), kscale=w.get("kscale"),
+                            forcing=w.get("F"), **opts)
+    integ.integrate(0.0, w["t_out"])
+    torch.cuda.synchronize()
+    y, st = integ.state(), integ.cell_stats()
+    rec = integ.step_record([0, 1, 5]) if opts.get("record_steps") else None
+    integ.close()
+    return y, st, rec
+
+
+def _cells(S, extra):
+    """Cells that the library packs (32 a CU up to 16 species, 64 above), and
+    ``extra`` more so that the last wave is partly filled."""
+    import torch
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    return (32 if S <= 16 else 64) * cu + extra
+
+
+@pytest.mark.parametrize("S,R,lu,sched", [(2, 3, 64, 1), (9, 30, 64, 0), (9, 30, 32, 1),
+                                          (12, 70, 64, 1), (16, 64, 64, 1), (16, 65, 32, 1),
+                                          (17, 30, 64, 1), (21, 84, 64, 0), (21, 130, 32, 1)])
+def test_packed_matches_one_cell_per_wave(oracle, parity, S, R, lu, sched):
+    m = W.synthetic_mechanism(S, R, 1)
+    n = _cells(S, 3)
+    c = W.cell_states(m, n, seed=11)
+    y0 = c["y0"]
+    y0[7, 0] = np.nan  # a failing cell among the others
+    w = dict(mechs=[m], T=c["T"], t_out=1e-8, y0=y0, rtol=1e-6, atol=1e-10)
+    y, st, _ = _run(w, y0, lu_precision=lu, scheduler=sched)
+    y1, st1, _ = _run(w, y0, lu_precision=lu, scheduler=sched, waves_per_simd=3)
+    assert st["status"][7] == -9 and np.all(np.delete(st["status"], 7) == 0)
+    assert np.array_equal(st, st1) and np.array_equal(y, y1, equal_nan=True)
+    k = np.r_[0:6, n - 30:n]
+    yo, _ = oracle.integrate([m], y0[k], 0.0, 1e-8, 1e-6, 1e-10, T=c["T"][k])
+    # (one whole cell of 36 may follow another valid step sequence, see conftest)
+    parity(y[k], yo, dict(w, y0=y0[k], T=c["T"][k]), f"S={S}", min_frac=0.95)
+
+
+def test_packed_generic_slots_forcing_scale_and_records(oracle):
+    """Robertson cells (empty and repeated slots) with rate scales and a forcing,
+    few allowed steps, and recorded steps."""
+    n = _cells(3, 1)
+    c = W.robertson_cells(n)
+    F = np.zeros((n, 3))
+    F[::3, 0] = 1e-3
+    w = dict(mechs=[W.robertson_mechanism()], kscale=c["kscale"], F=F, t_out=40.0)
+    for opts in (dict(), dict(max_steps=60), dict(record_steps=400)):
+        y, st, rec = _run(w, c["y0"], **opts)
+        y1, st1, rec1 = _run(w, c["y0"], waves_per_simd=3, **opts)
+        assert np.array_equal(st, st1) and np.array_equal(y, y1)
+        # 60 steps are too few for every cell, 400 recorded ones for some
+        assert set(np.unique(st["status"])) <= ({-1} if "max_steps" in opts else
+                                                {0, -10} if "record_steps" in opts else {0})
+        for a, b in zip(rec or [], rec1 or []):
+            assert all(np.array_equal(a[key], b[key]) for key in a)
