@@ -146,6 +146,7 @@ struct Bin {
   // launch shape: from the options, or chosen by bdfx_autotune()
   int32_t waves_per_simd = 0, waves_per_block = 1, queue_chunk = 1, cells_per_wave = 1;
   bool tuned = false;
+  int budget = 0;  // register budget in effect: waves_per_simd, or the library's choice (budget_of)
   int packed = 1;  // cells per wave of the packed kernel in effect (1: k_integrate)
   int tab = bdfx::kTabLds;  // placement of the reaction tables (bdfx::kTab*)
   int64_t tune_sample = 0;  // bdfx_autotune(): cells timed and time of the pick
@@ -649,8 +650,58 @@ static hipError_t launch_bin(bdfx_ctx ctx, const Bin &b, bdfx::Params P) {
   const bdfx_mech m = ctx->mechs[b.mech];
   P.lds_doubles = b.lds_doubles;
   if (b.packed > 1) return b.se->launch_packed(P, fp32, m->abc, b.cfg, ctx->stream);
-  return b.se->launch(P, fp32, b.waves_per_simd, b.tab, b.cells_per_wave, kernel_flags(ctx, m),
-                      b.cfg, ctx->stream);
+  return b.se->launch(P, fp32, b.budget, b.tab, b.cells_per_wave, kernel_flags(ctx, m), b.cfg,
+                      ctx->stream);
+}
+
+// The register budget for as many waves per SIMD as help once there are more
+// cells than waves, or 0 where the compiler's own choice stays the best.  Ms at
+// 16,384 cells (21 species and GMRES: 8,192), compiler's choice -> that budget:
+//   9 species non-isothermal   FP64 21.0 -> 15.6   FP32 16.0 -> 14.2
+//   9 species, difference quotients  FP64 14.6 -> 13.0   FP32 12.3 -> 11.5
+//   21 species                 FP64 12.8 -> 12.1   FP32 11.9 -> 11.4
+//   21 species, difference quotients  FP64 33.5 -> 30.6 (16,384 cells)
+//   21 species, GMRES          9.4 -> 8.7
+//   30 species, 4 waves        FP64 34.1 -> 33.3   FP32 35.5 -> 33.0  (5: 34.0, 35.0)
+//   30 species, difference quotients, 4 waves      FP32 46.6 -> 44.5
+//   21 species non-isothermal (the 32-entry kernel), 4 waves  FP32 33.5 -> 30.4
+// It stays for FP64 in the 32-entry kernel with the temperature or difference
+// quotients (33.4 -> 33.9, 52.3 -> 53.3) and for 21 species with FP32
+// difference quotients (9.8 -> 10.0 at 4,096 cells), where the smaller budgets
+// spill, and above 32 species, where the LDS or the matrix in registers bounds
+// the waves.
+static int most_waves(int S, bool fp32, bool thermal, int lin) {
+  if (S > 32) return 0;
+  const bool dq = lin == bdfx::kLinDq;
+  if (S > 21) return !fp32 && (thermal || dq) ? 0 : 4;
+  return dq && fp32 && S > 16 ? 0 : 5;
+}
+
+// Register budget of a one-cell-per-wave launch.  With the registers the
+// compiler likes best a cell's steps are fastest (64 cells of 21 species: 3.75
+// ms against 4.12 and 4.28 at the 4- and 5-wave budgets), which is what counts
+// while every cell has a resident wave of its own.  Beyond, resident waves
+// count: just enough of them for the cells, up to most_waves.  The budgets'
+// kernels give the same bits.
+static int budget_of(bdfx_ctx ctx, const Bin &b, int waves, size_t lds_bytes, int *budget) {
+  *budget = b.waves_per_simd;
+  const bdfx_mech m = ctx->mechs[b.mech];
+  const bool fp32 = ctx->opt.lu_precision == 32;
+  const int most = most_waves(b.se->S, fp32, m->thermal, lin_of(ctx));
+  const int64_t simds = 4 * static_cast<int64_t>(ctx->n_cu);
+  // (two waves a SIMD fit whatever the compiler took)
+  if (b.waves_per_simd != 0 || most == 0 || b.cells_per_wave != 1 || ctx->opt.lockstep > 0 ||
+      lds_bytes > 65536 || b.count <= 2 * simds)
+    return BDFX_OK;
+  int occ0 = 0, occ = 0;
+  HIPCHK(ctx, b.se->occupancy(fp32, 0, bdfx::kTabLds, 1, kernel_flags(ctx, m), bdfx::kWave * waves,
+                              lds_bytes, &occ0));
+  if (b.count <= static_cast<int64_t>(occ0) * waves * ctx->n_cu) return BDFX_OK;
+  const int w = static_cast<int>(std::min<int64_t>((b.count + simds - 1) / simds, most));
+  HIPCHK(ctx, b.se->occupancy(fp32, w, bdfx::kTabLds, 1, kernel_flags(ctx, m), bdfx::kWave * waves,
+                              lds_bytes, &occ));
+  if (occ > occ0) *budget = w;
+  return BDFX_OK;
 }
 
 // Kernel, LDS size and grid of one bin from its launch shape.
@@ -690,6 +741,9 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
   size_t lds[3];
   int64_t grid[3] = {0, 0, 0};
   const int tail = bdfx::inv_tail(b.se->S, fp32 ? 4 : 8, m->thermal, lin_of(ctx), lock > 0, cpw);
+  const size_t wave_lds = align_up(bdfx::lds_doubles(b.se->S, m->R, fp32 ? 4 : 8, bdfx::kTabLds, m->thermal,
+                                                     ctx->opt.gmres_maxl, tail), 2) * 8;
+  if (const int rc = budget_of(ctx, b, waves, waves * wave_lds, &b.budget)) return rc;
   for (int k : {bdfx::kTabLds, bdfx::kTabRxGlobal, bdfx::kTabGlobal}) {
     const int32_t d = static_cast<int32_t>(
         align_up(bdfx::lds_doubles(b.se->S, m->R, fp32 ? 4 : 8, k, m->thermal,
@@ -699,8 +753,8 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
     if (lds[k] > 65536 || (k != bdfx::kTabLds && cpw != 1) || (k == bdfx::kTabGlobal && !queue) ||
         (k != bdfx::kTabLds && lock > 0))
       continue;
-    HIPCHK(ctx, b.se->occupancy(fp32, b.waves_per_simd, k, cpw, kernel_flags(ctx, m), b.cfg.block,
-                                lds[k], &occ[k]));
+    HIPCHK(ctx, b.se->occupancy(fp32, b.budget, k, cpw, kernel_flags(ctx, m), b.cfg.block, lds[k],
+                                &occ[k]));
     if (queue) {
       const int per_cu = ctx->opt.blocks_per_cu > 0 ? ctx->opt.blocks_per_cu : std::max(occ[k], 1);
       grid[k] = std::min<int64_t>(static_cast<int64_t>(per_cu) * ctx->n_cu, need);
@@ -760,8 +814,8 @@ static int configure_pair(bdfx_ctx ctx) {
   if (a.lds_doubles < lds_b) return BDFX_OK;
   // A-waves per CU in bin A's own launch
   int occ_a = 0;
-  HIPCHK(ctx, a.se->occupancy(fp32, a.waves_per_simd, a.tab, 1, kernel_flags(ctx, ma),
-                              a.cfg.block, a.cfg.lds_bytes, &occ_a));
+  HIPCHK(ctx, a.se->occupancy(fp32, a.budget, a.tab, 1, kernel_flags(ctx, ma), a.cfg.block,
+                              a.cfg.lds_bytes, &occ_a));
   const int a_per_cu = occ_a * std::max(a.waves_per_block, 1);
   int best_a = 0, best_b = 0, best_wa = 0, best_wb = 0, best_occ = 0;
   // (wb = 0: blocks of larger-mechanism waves only, which take the smaller
