@@ -125,13 +125,21 @@ typedef struct {
   int32_t waves_per_block; /* 0 = library choice / autotuned value */
   int32_t blocks_per_cu;   /* persistent grid: resident blocks per CU (0 = auto) */
   int32_t queue_chunk;     /* cells per work-queue pop (0 = 1) */
-  int32_t waves_per_simd;  /* register budget of the integrator kernel: 0 = compiler's
-                              choice, 3, 4 or 5 = code built for that many resident waves
-                              per SIMD (at most 168 / 128 / 96 VGPRs, spilling if needed;
-                              the one-launch pair of BDFX_SCHED_FUSED has no 5-wave code
-                              and then runs as two launches) */
+  int32_t waves_per_simd;  /* register budget of the integrator kernel: 0 = the library's
+                              choice by the number of cells, 3, 4 or 5 = code built for that
+                              many resident waves per SIMD (at most 168 / 128 / 96 VGPRs,
+                              spilling if needed; above 32 species with a Newton matrix the
+                              code for two (FP64) or three (FP32) waves stands in for the
+                              larger budgets, whose waves would not fit; the one-launch pair
+                              of BDFX_SCHED_FUSED has no 5-wave code and then runs as two
+                              launches).  Results do not depend on it, bit for bit */
   int32_t cells_per_wave;  /* 0 or 1; 2 = each half-wave integrates its own cell
-                              (mechanisms of at most 32 species) */
+                              (mechanisms of at most 32 species).  With 0 or 1 and
+                              waves_per_simd = 0 the library puts two or four isothermal
+                              cells of at most 21 species on a wave, each on its own lanes,
+                              where the cells are many (analytic Jacobian, no lock-step, no
+                              checkpoints); the results are those of one cell per wave,
+                              bit for bit */
   int32_t jacobian;        /* BDFX_JAC_ANALYTIC (0) or BDFX_JAC_DQ (1): Newton matrix from
                               forward difference quotients, one right-hand side per state
                               entry (Table 1, approaches 3A/3B) */
@@ -388,7 +396,8 @@ typedef struct {
   int32_t queue_chunk;     /* cells per work-queue pop, >= 1 */
   int64_t sample_cells;    /* bdfx_autotune(): cells timed */
   float ms;                /* bdfx_autotune(): time of the fastest shape on the sample */
-  int32_t cells_per_wave;  /* 1, or 2 for mechanisms of at most 32 species */
+  int32_t cells_per_wave;  /* as bdfx_options.cells_per_wave: 1, or 2 for mechanisms of at
+                              most 32 species */
   int32_t tables;          /* out: where the reaction tables of this launch live, chosen by
                               occupancy: 1 all in LDS; 0 slot words read from global memory;
                               2 slot words and the cell's rate constants in global memory

@@ -10,15 +10,16 @@
 // Unlike the paper's host-driven lock-step batches (Sec. 2), step size and
 // order are chosen per cell, entirely on the device.
 //
-// Mapping: one wavefront (64 lanes) per cell.  Lane i owns species i: its
-// Nordsieck entries z_j[i], Newton correction, error weight and, during a
-// setup, row i of the Newton matrix in registers.  Everything that is a
+// Mapping: one wavefront (64 lanes) per cell (bdf_packed.h: two or four cells).
+// Lane i owns species i: its Nordsieck entries z_j[i], Newton correction and
+// error weight.  During a setup the Newton matrix is in registers, one row per
+// lane up to 16 species and in matrix-core tiles above.  Everything that is a
 // property of the cell (t, h, q, counters, Newton rate, ...) is wave-uniform:
 // reductions are DPP row operations plus row broadcasts, broadcasts are
 // v_readlane, branches are scalar, so the integrator's control flow never
 // diverges inside a wave.  Per-cell data that is gathered by index (current
 // state, rate constants, the right-hand side accumulator, the control block
-// and the LU factors) lives in LDS.  Reactions are distributed over lanes;
+// and the inverse Newton matrix) lives in LDS.  Reactions are distributed over lanes;
 // their rates are scattered into f with LDS FP64 atomics.
 //
 // Readings of the paper where it is silent are the same as the CPU oracle's
@@ -851,7 +852,7 @@ __device__ __forceinline__ double rhs(const MechDev &m, const Lds &L, const Grp<
 // the Newton matrix in registers
 // ---------------------------------------------------------------------------
 
-// Row i in lane i (gj_invert below): at most 16 species, or two cells per wave.
+// Row i in lane i (gj_step below): at most 16 species, or two cells per wave.
 template <int S, typename LT>
 struct RowMat {
   LT a[S];
@@ -1221,7 +1222,7 @@ __device__ __forceinline__ void dq_matrix(Mat<S, LT, G> &a, const MechDev &m, co
 }
 
 // ---------------------------------------------------------------------------
-// dense LU with partial pivoting, one row per lane
+// Gauss-Jordan elimination with partial pivoting, one row per lane
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ uint64_t abs_key(double v) {
@@ -1306,26 +1307,13 @@ __device__ __forceinline__ void gj_step(LT (&a)[S], const Grp<G> &W, int k, int 
     zero_pivot = kmax <= 1u;
   } else {
     // exact 64-bit maximum in two 32-bit passes: high words, then the low
-    // words of the lanes that tie on the high word.  With one cell per wave
-    // and S > 16, a high word held by one lane only decides alone (the
-    // low-word pass would return that lane, and its key is not zero); ties,
-    // the all-zero column among them, take the second pass.  (The smallest
-    // kernels, whose elimination is a minor cost, stay without the extra
-    // branch: it costs them spilled registers.)
-    constexpr bool kShortcut = G == 1 && S > 16;
+    // words of the lanes that tie on the high word
     const uint64_t key = piv < 0 ? abs_key(a[E]) : 0ull;
     const uint32_t hi = static_cast<uint32_t>(key >> 32), lo = static_cast<uint32_t>(key);
     const uint32_t hmax = W.template max_u32<(S + 15) / 16>(hi);
-    uint64_t tie = 0;
-    if constexpr (kShortcut) tie = __ballot(hi == hmax);
-    if (kShortcut && __builtin_popcountll(tie) == 1) {
-      p = __builtin_ctzll(tie);
-      zero_pivot = false;
-    } else {
-      const uint32_t lmax = W.template max_u32<(S + 15) / 16>(hi == hmax ? lo : 0u);
-      p = W.first(hi == hmax && lo == lmax);
-      zero_pivot = hmax == 0u && lmax <= 1u;
-    }
+    const uint32_t lmax = W.template max_u32<(S + 15) / 16>(hi == hmax ? lo : 0u);
+    p = W.first(hi == hmax && lo == lmax);
+    zero_pivot = hmax == 0u && lmax <= 1u;
   }
   if (zero_pivot && info == 0) info = k + 1;
   const bool is_p = W.lane == p;
@@ -1370,28 +1358,19 @@ __device__ __forceinline__ void gj_block(LT (&a)[S], const Grp<G> &W, int k0, in
 
 // Inverts the cell's S x S Newton matrix M (row i in lane i's registers) by
 // Gauss-Jordan elimination with partial pivoting (gj_step), in blocks of four
-// (eight above 32 species) steps whose slot indices are static, so the block
-// loop need not be unrolled (at S = 53 the unrolled form would not fit the
-// instruction cache) and only the last step of a block writes its row to
-// rotated slots.  After S steps slot k
-// holds the inverse column of step k, i.e. column p_k.  M^{-1} is written to
-// LDS in natural order, column-major (entry (r, c) at c*S + r), so that a
-// solve is one lane-parallel matrix-vector product.  T > 0: M^{-1} is kept in
-// slot order instead ((r, k) at k*S + r holds M^{-1}(r, p_k)), slots 0 .. S-T-1
-// in LDS and the last T in registers of lane r (moved there from the lane
-// that computed row r by ds_bpermute), so the LDS area is (S - T) S entries.
-// Returns 0, or k+1 for the first column k without a nonzero pivot (the
-// elimination then runs on garbage).
+// steps whose slot indices are static, so the block loop need not be unrolled
+// and only the last step of a block writes its row to rotated slots.  After S
+// steps slot k holds the inverse column of step k, i.e. column p_k.  M^{-1} is
+// written to LDS in natural order, column-major (entry (r, c) at c*S + r), so
+// that a solve is one lane-parallel matrix-vector product.  Returns 0, or k+1
+// for the first column k without a nonzero pivot (the elimination then runs on
+// garbage).
 template <int S, typename LT, int T = 0, int G>
 __device__ __forceinline__ int invert(RowMat<S, LT> &m, const Grp<G> &W, const Lds &L, int n,
                                       InvTail<T, LT> *tail = nullptr) {
-  static_assert(T == 0, "an inverse tail needs the tiled form");
+  static_assert(T == 0 && S <= 32, "larger matrices take the tiled form");
   LT (&a)[S] = m.a;
-  // steps per block (one register rotation per block): eight above 32
-  // species, where the rotation's S moves are a larger share; sixteen
-  // steps made the 53-species FP64 kernels' loop too large for the
-  // instruction cache (27 % slower), eight at 21 species gained nothing
-  constexpr int B = S > 32 ? 8 : 4;
+  constexpr int B = 4;  // steps per block (one register rotation each)
   int piv = W.lane < S ? -1 : 1 << 20;
   int info = 0;
   LT dinv = static_cast<LT>(1);  // 1 / own pivot
@@ -1651,7 +1630,21 @@ __device__ __forceinline__ void mx_tile_row(TileMat<S, LT> &m, const Grp<1> &W, 
 // Inverts the cell's Newton matrix held in tiles; results as invert() of a
 // RowMat (same pivots, same arithmetic).  The first n rows and columns are
 // eliminated; the padding beyond them is an identity, whose elimination changes
-// nothing.
+// nothing.  T > 0: M^{-1} is kept in slot order instead ((r, k) at k*S + r holds
+// M^{-1}(r, p_k)), slots 0 .. S-T-1 in LDS and the last T in registers of lane
+// r, so the LDS area is (S - T) S entries.
+//
+// Why tiles: one row per lane issues, for every step and entry, two lane reads
+// and one FMA (S^2 x 3 instructions per step, S of 64 lanes in use), which was
+// 55 % of the 53-species kernel's instructions.  In tiles four steps take one
+// matrix instruction per 16 x 16 tile, and what is left is the serial chain of
+// the steps on the four own columns: pivot search, reciprocal and three FMAs,
+// about 450 clocks a step.  Per inverse, us, before -> now: one wave per SIMD,
+// 53 species FP64 34.5 -> 26.0, 64 species 49.5 -> 26.8; three waves per SIMD,
+// 53 species FP32 56.3 -> 32.1, 21 species FP64 17.3 -> 11.8, FP32 10.9 -> 7.4.
+// 53 species FP64: 2,040 -> 1,287 instructions per cell and step, 43.2 -> 37.8 ms
+// for 8,192 cells.  Up to 16 species there is one tile, mostly padding, and a
+// row holds few entries: rows stay.
 template <int S, typename LT, int T = 0>
 __device__ __forceinline__ int invert(TileMat<S, LT> &m, const Grp<1> &W, const Lds &L, int n,
                                       InvTail<T, LT> *tail = nullptr) {
@@ -1747,7 +1740,7 @@ __device__ __forceinline__ int invert(TileMat<S, LT> &m, const Grp<1> &W, const 
 
 // x = M^{-1} b with the inverse in LDS; lane i passes b_i and gets x_i.
 // SPLIT: three partial sums (FP32 inverse of isothermal kernels, see below).
-// T > 0 (gj_invert's slot order with a register tail): the sum runs over the
+// T > 0 (slot order with a register tail, invert()): the sum runs over the
 // slots k, b_{p_k} gathered to lane k first.
 template <int S, typename LT, bool SPLIT, int T = 0, int G>
 __device__ __forceinline__ double inv_solve(const Lds &L, const Grp<G> &W, double b,

@@ -1,18 +1,22 @@
-// bdf_packed.h -- several cells per wave for mechanisms of at most 32 species.
+// bdf_packed.h -- several cells per wave for mechanisms of at most 21 species.
 //
 // k_integrate gives a cell the whole wave, of which a small mechanism uses S of
 // 64 lanes, and computes every per-cell scalar of the step control (t, h, xi_i,
 // l_j, gamma, norms, eta) at wave width.  Here a wave integrates G cells, one
 // per group of 64 / G lanes (lane i of a group owns species i): the vector work
 // of one step, and the scalar work that is bound to it, is issued once for G
-// cells.  The kernels are bound by VALU issue, so that is where the time goes.
+// cells.  The kernels are bound by VALU issue (77 to 85 % busy at 4 or 5 waves per
+// SIMD), so that is where the time goes.  One cell per wave -> packed: 9 species,
+// 131,072 cells 74.7 -> 43.4 ms; 3 species, 65,536 cells 14.7 -> 8.3 ms; 21
+// species, 262,144 cells 333 -> 271 ms.  What is left is above all the setups
+// (55 % of the instructions at 21 species, 42 % at 9), which run a cell at a time.
 //
 // Two things make the groups worth their divergence.  The loop runs over step
 // *attempts*, not over cells: a group whose cell is finished writes it and takes
 // its next cell while the others go on, so no group waits for the longest cell
 // of its wave.  And a setup is not run under a group's exec mask: the wave
 // visits the groups that need one and forms and inverts that cell's Newton
-// matrix with all 64 lanes (newton_matrix, gj_invert of one cell per wave), so
+// matrix with all 64 lanes (newton_matrix and invert of one cell per wave), so
 // its cost per cell is the one of k_integrate.
 //
 // Every operation of a cell is the one k_integrate does, in its order (the
