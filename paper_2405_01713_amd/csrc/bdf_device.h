@@ -2503,7 +2503,10 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
 // recorded state.  d f / d lnA_r = nu_r q_r.
 
 // (J^T v)_i for lane i, and pbar_r += scale q_r(y) (nu_r . v) (reaction r
-// on lane r mod 64, accumulated in LDS).  vb: a 64-entry LDS buffer.
+// on lane r mod 64, accumulated in LDS).  vb: a 64-entry LDS buffer.  ABC: every
+// reaction A + B <=> C, the same bits (the general path's further factors are
+// ones and its further terms zeros).
+template <bool ABC>
 __device__ __forceinline__ double adj_scatter(const MechDev &m, const Lds &L, double *vb,
                                               double *pb, int li, double yi, double vi,
                                               double scale, bool want_jtv) {
@@ -2521,12 +2524,18 @@ __device__ __forceinline__ double adj_scatter(const MechDev &m, const Lds &L, do
       a[k] = slot_species(w.x, k);
       b[k] = slot_species(w.y, k);
       // empty slots read yb = 1 and vb = 0 at kEmptySlot
-      pf *= L.yb[a[k]];
-      s -= vb[a[k]];
-      pr *= L.yb[b[k]];
-      s += vb[b[k]];
+      if (!ABC || k < 2) {
+        pf *= L.yb[a[k]];
+        s -= vb[a[k]];
+      }
+      if (!ABC || k < 1) {
+        pr *= L.yb[b[k]];
+        s += vb[b[k]];
+      }
     }
-    pb[r] += scale * (pf + pr) * s;
+    // (ABC: the general path's last factors are ones, so that a fused sum there
+    // adds two rounded products)
+    pb[r] += scale * (ABC ? plain_sum(pf, pr) : pf + pr) * s;
     if (want_jtv) {
       // d q_r / d y_j for each slot: the side's constant times the other slots
 #pragma unroll
@@ -2589,7 +2598,7 @@ __device__ __forceinline__ void rec_coeffs(const RecView &rv, int n, double hpad
 // else the state is parked for the call that sweeps the steps before lo.  The
 // sums run in step order either way, so a sweep in pieces equals one sweep
 // over all steps bit for bit.
-template <int S>
+template <int S, bool ABC>
 __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int li, double *lds,
                                               const RecView &rv, int hi, int lo, bool init) {
   const MechDev &m = P.mech;
@@ -2650,11 +2659,11 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
     // (I - gamma J(y_n))^T mu = eb
     {
       Mat<S, double, 1> a;
-      newton_matrix<S, double>(a, m, L, W1, yn, gamma, true);
+      newton_matrix<S, double, ABC>(a, m, L, W1, yn, gamma, true);
       invert<S, double>(a, W1, L, n);
     }
     const double mu = own ? inv_solve<S, double, false>(L, W1, eb) : 0.0;
-    adj_scatter(m, L, vb, pb, li, yn, mu, gamma, false);
+    adj_scatter<ABC>(m, L, vb, pb, li, yn, mu, gamma, false);
     // a = zp_0 - zp_1 / l_1
     zb[0] += mu;
     zb[1] -= mu / l[1];
@@ -2668,7 +2677,7 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
     if (step == 1) {
       // z = [y0, h_1 f(y0)]
       const double y0 = own ? P.rec_y0[cell * stride + li] : 0.0;
-      const double jtv = adj_scatter(m, L, vb, pb, li, y0, zb[1], hn, true);
+      const double jtv = adj_scatter<ABC>(m, L, vb, pb, li, y0, zb[1], hn, true);
       y0bar = zb[0] + hn * jtv;
       break;
     }
@@ -2676,7 +2685,7 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
     if (qr >> 8) {
       // z was rebuilt as [y_{n-1}, h_n f(y_{n-1})] before this step
       const double yp = own ? rv.row(step - 1)[li] : 0.0;
-      const double jtv = adj_scatter(m, L, vb, pb, li, yp, zb[1], hn, true);
+      const double jtv = adj_scatter<ABC>(m, L, vb, pb, li, yp, zb[1], hn, true);
       zb[0] += hn * jtv;
 #pragma unroll
       for (int j = 1; j <= kQmax; ++j) zb[j] = 0.0;
@@ -2772,14 +2781,14 @@ __device__ __forceinline__ void rerun_segment(const Params &P, int64_t cell, con
 }
 
 // Pass j, second half: sweep the rerun segment.
-template <int S>
+template <int S, bool ABC>
 __device__ __forceinline__ void sweep_segment(const Params &P, int64_t cell, int li, double *lds,
                                               int j) {
   const int nseg = adj_segments(P, cell);
   if (j >= nseg) return;
   const int N = uni(P.rec_n[cell]);
   const int K = P.ckpt_every, c = nseg - 1 - j, n0 = c * K;
-  adjoint_steps<S>(P, cell, li, lds, adj_rows(P, cell, n0), n0 + K < N ? n0 + K : N, n0 + 1, j == 0);
+  adjoint_steps<S, ABC>(P, cell, li, lds, adj_rows(P, cell, n0), n0 + K < N ? n0 + K : N, n0 + 1, j == 0);
 }
 
 __host__ __device__ constexpr int lds_doubles_adjoint(int S, int R) {

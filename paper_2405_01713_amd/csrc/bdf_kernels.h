@@ -158,13 +158,19 @@ const void *pair_kernel(bool fp32, int minw, int taba) {
   return t[fp32 ? 1 : 0][taba];
 }
 
-// Adjoint sweep over a full record: one wave per cell.
+// Adjoint sweep over a full record: one wave per cell.  A step is the Newton
+// matrix of M^T, its inverse, one solve and two passes over the reactions; bound
+// by the issue of those instructions, half of them the inverse's.  ABC as in
+// k_integrate: the general slot loops issue each of the 36 slot pairs of a
+// reaction under its own mask where A + B <=> C has nine.  Value and gradient,
+// general -> ABC: 21 species, 4,096 cells 30.2 -> 29.1 ms, 256 cells 10.7 -> 10.0;
+// 53 species, 512 cells 45.7 -> 43.2.
 // Waves per SIMD the adjoint kernels' registers must allow (1: compiler's
 // choice).  At 21 species the tiled elimination takes 100 to 110 registers, so
 // four; without a bound it took 153.
 __host__ __device__ constexpr int adjoint_waves(int S) { return S > 32 ? 2 : S > 16 ? 4 : 1; }
 
-template <int S>
+template <int S, bool ABC>
 __global__ void __launch_bounds__(256, adjoint_waves(S)) k_adjoint(Params P) {
   extern __shared__ double smem[];
   const int wib = uni(static_cast<int>(threadIdx.x / kWave));
@@ -173,8 +179,8 @@ __global__ void __launch_bounds__(256, adjoint_waves(S)) k_adjoint(Params P) {
   if (w >= P.n_list) return;
   const int64_t cell = P.list ? P.list[w] : w;
   const RecView rv{P.rec + cell * P.rec_cap * P.rec_stride, 1, P.rec_stride};
-  adjoint_steps<S>(P, cell, li, smem + static_cast<int64_t>(wib) * P.lds_doubles, rv,
-                   uni(P.rec_n[cell]), 1, true);
+  adjoint_steps<S, ABC>(P, cell, li, smem + static_cast<int64_t>(wib) * P.lds_doubles, rv,
+                        uni(P.rec_n[cell]), 1, true);
 }
 
 // Pass j of the sweep over checkpointed records, as two launches: k_adj_rerun
@@ -193,21 +199,21 @@ __global__ void __launch_bounds__(256, adjoint_waves(S)) k_adj_rerun(Params P, i
   rerun_segment<S, ABC>(P, P.list ? P.list[w] : w, W, smem + static_cast<int64_t>(wib) * P.lds_doubles, j);
 }
 
-template <int S>
+template <int S, bool ABC>
 __global__ void __launch_bounds__(256, adjoint_waves(S)) k_adj_sweep(Params P, int j) {
   extern __shared__ double smem[];
   const int wib = uni(static_cast<int>(threadIdx.x / kWave));
   const int li = threadIdx.x & (kWave - 1);
   const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wib;
   if (w >= P.n_list) return;
-  sweep_segment<S>(P, P.list ? P.list[w] : w, li, smem + static_cast<int64_t>(wib) * P.lds_doubles, j);
+  sweep_segment<S, ABC>(P, P.list ? P.list[w] : w, li, smem + static_cast<int64_t>(wib) * P.lds_doubles, j);
 }
 
 // kind 0: full-record sweep; 1: segment rerun; 2: segment sweep
 template <int S>
 const void *adjoint_kernel(int kind, bool abc) {
-  if (kind == 0) return (const void *)&k_adjoint<S>;
-  if (kind == 2) return (const void *)&k_adj_sweep<S>;
+  if (kind == 0) return abc ? (const void *)&k_adjoint<S, true> : (const void *)&k_adjoint<S, false>;
+  if (kind == 2) return abc ? (const void *)&k_adj_sweep<S, true> : (const void *)&k_adj_sweep<S, false>;
   return abc ? (const void *)&k_adj_rerun<S, true> : (const void *)&k_adj_rerun<S, false>;
 }
 
