@@ -471,8 +471,8 @@ __device__ __forceinline__ void bdf_coeffs(int q, const double (&xi)[kQmax + 2],
 // xi_i = (h + h_1 + ... + h_{i-1}) / h and its reciprocal, lane j the
 // coefficient l_j, which takes the factors (1 + x/xi_i) in turn from its
 // neighbour's.  The operations of bdf_coeffs on each entry.  Every lane gets
-// l_1 and Cerr.
-template <int G>
+// l_1 and Cerr.  DIV: xi_i by a division instead of the product with 1 / h.
+template <bool DIV = false, int G>
 __device__ __forceinline__ void step_coeffs(int q, double h, double *C, const double *hist, int kxi,
                                             int kl, const Grp<G> &W, double &l1, double &Cerr) {
   const int i = local_lane(W).lane;
@@ -482,8 +482,7 @@ __device__ __forceinline__ void step_coeffs(int q, double h, double *C, const do
     const double hk = hist[k];
     sum = plain_sum(sum, i >= k + 2 ? hk : 0.0);
   }
-  const double rh = rcp(h);
-  double xi = sum * rh;
+  double xi = DIV ? sum / h : sum * rcp(h);
   if (i > q + 1 || i == 0) xi = 0.0;
   if (i == 1) xi = 1.0;
   const double rxi = rcp(xi);
@@ -2573,23 +2572,6 @@ struct RecView {
   __device__ const double *row(int s) const { return p + static_cast<int64_t>(s - first) * stride; }
 };
 
-// xi_i and l_j of recorded step `step` (1-based); hist from the records.
-__device__ __forceinline__ void rec_coeffs(const RecView &rv, int n, double hpad, int step, int q,
-                                           double (&xi)[kQmax + 2], double (&l)[kQmax + 2],
-                                           double &Cerr) {
-  const double hn = rv.row(step)[n];
-  double sum = hn;
-  xi[0] = 0.0;
-  xi[1] = 1.0;
-#pragma unroll
-  for (int i = 2; i <= kQmax + 1; ++i) {
-    const int idx = step - i + 1;  // 1-based step of h_{n-i+1}
-    sum += idx >= 1 ? rv.row(idx)[n] : hpad;
-    xi[i] = i <= q + 1 ? sum / hn : 0.0;
-  }
-  bdf_coeffs(q, xi, l, Cerr);
-}
-
 // Sweeps steps hi down to lo (1 <= lo, hi <= the cell's step count) of one
 // cell through the rows rv.  init: the sweep starts at the cell's last step
 // from dL/dy(t_out); else from the state an earlier call parked (P.adj: the
@@ -2597,7 +2579,10 @@ __device__ __forceinline__ void rec_coeffs(const RecView &rv, int n, double hpad
 // dL/dlnA sums).  lo == 1 finishes the cell (dL/dy0 and dL/dlnA written),
 // else the state is parked for the call that sweeps the steps before lo.  The
 // sums run in step order either way, so a sweep in pieces equals one sweep
-// over all steps bit for bit.
+// over all steps bit for bit.  The steps are one serial chain: what a step needs
+// of its row (state entry by lane, order word, and on lane k the size of the
+// step k before it) is loaded while the step after it is swept, and its
+// coefficients are formed by lane (step_coeffs).
 template <int S, bool ABC>
 __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int li, double *lds,
                                               const RecView &rv, int hi, int lo, bool init) {
@@ -2642,14 +2627,42 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
   }
   double y0bar = zb[0];
 
+  double *C = L.C;
+  auto y_of = [&](int s) { return own ? rv.row(s)[li] : 0.0; };
+  auto h_of = [&](int s) {
+    return li > kQmax ? 0.0 : s - li >= 1 ? rv.row(s - li)[n] : hpad;
+  };
+  // xi and l of the step with sizes h (h_of) and order q, into C
+  auto coeffs = [&](int q, double h) {
+    wave_lds_sync();
+    if (li >= 1 && li <= kQmax) C[Ctl::kHist + li - 1] = h;
+    wave_lds_sync();
+    double l1, Cerr;
+    step_coeffs<true>(q, uni(W1.bcast(h, 0)), C, C + Ctl::kHist, Ctl::kXi, Ctl::kL, W1, l1, Cerr);
+    wave_lds_sync();
+  };
+  int in_C = 0;  // step whose coefficients C holds
+  double yn = 0.0, hs = 0.0, qd = 0.0;
+  if (hi >= lo) {
+    yn = y_of(hi);
+    hs = h_of(hi);
+    qd = rv.row(hi)[n + 1];
+  }
   for (int step = hi; step >= lo; --step) {
-    const int qr = uni(static_cast<int>(rv.row(step)[n + 1]));
+    const int qr = uni(static_cast<int>(qd));
     const int q = qr & 255;
-    const double hn = uni(rv.row(step)[n]);
-    double xi[kQmax + 2], l[kQmax + 2], Cerr;
-    rec_coeffs(rv, n, hpad, step, q, xi, l, Cerr);
+    const double hn = uni(W1.bcast(hs, 0));
+    if (in_C != step) coeffs(q, hs);
+    double yp = 0.0;
+    if (step > 1) {
+      yp = y_of(step - 1);
+      hs = h_of(step - 1);
+      qd = rv.row(step - 1)[n + 1];
+    }
+    double l[kQmax + 1];
+#pragma unroll
+    for (int j = 0; j <= kQmax; ++j) l[j] = C[Ctl::kL + j];
     const double gamma = uni(hn / l[1]);
-    const double yn = own ? rv.row(step)[li] : 0.0;
     // z_n = zp + l e, e = y_n - zp_0
     double eb = ebx;
 #pragma unroll
@@ -2681,16 +2694,15 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
       y0bar = zb[0] + hn * jtv;
       break;
     }
-    const int qp = uni(static_cast<int>(rv.row(step - 1)[n + 1])) & 255;
+    const int qp = uni(static_cast<int>(qd)) & 255;
     if (qr >> 8) {
       // z was rebuilt as [y_{n-1}, h_n f(y_{n-1})] before this step
-      const double yp = own ? rv.row(step - 1)[li] : 0.0;
       const double jtv = adj_scatter<ABC>(m, L, vb, pb, li, yp, zb[1], hn, true);
       zb[0] += hn * jtv;
 #pragma unroll
       for (int j = 1; j <= kQmax; ++j) zb[j] = 0.0;
     } else {
-      const double eta = uni(hn / rv.row(step - 1)[n]);
+      const double eta = uni(hn / W1.bcast(hs, 0));
       double fct = 1.0;
 #pragma unroll
       for (int j = 1; j <= kQmax; ++j) {
@@ -2698,13 +2710,13 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
         if (j <= q) zb[j] *= fct;
       }
       if (q == qp + 1 || q == qp - 1) {
-        double xip[kQmax + 2], lp[kQmax + 2], Cp;
-        rec_coeffs(rv, n, hpad, step - 1, qp, xip, lp, Cp);
+        coeffs(qp, hs);
+        in_C = step - 1;
         if (q == qp + 1) {
-          const double c = 1.0 / pick(xip, qp + 1);
+          const double c = 1.0 / C[Ctl::kXi + qp + 1];
 #pragma unroll
           for (int j = 1; j <= kQmax; ++j)
-            if (j <= qp + 1) ebx += c * lp[j - 1] * zb[j];
+            if (j <= qp + 1) ebx += c * C[Ctl::kL + j - 1] * zb[j];
 #pragma unroll
           for (int j = 1; j <= kQmax; ++j)
             if (j == qp + 1) zb[j] = 0.0;
@@ -2717,7 +2729,7 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
           for (int i = 1; i <= kQmax - 1; ++i)
             if (i <= qp - 1) {
 #pragma unroll
-              for (int j = i + 1; j >= 1; --j) c[j] = c[j - 1] + xip[i] * c[j];
+              for (int j = i + 1; j >= 1; --j) c[j] = c[j - 1] + C[Ctl::kXi + i] * c[j];
             }
           double acc = 0.0;
 #pragma unroll
@@ -2729,6 +2741,7 @@ __device__ __forceinline__ void adjoint_steps(const Params &P, int64_t cell, int
         }
       }
     }
+    yn = yp;
   }
   if (lo == 1) {
     if (own) P.y0bar[cell * P.ldy + li] = y0bar;

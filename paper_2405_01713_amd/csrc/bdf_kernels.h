@@ -163,8 +163,9 @@ const void *pair_kernel(bool fp32, int minw, int taba) {
 // by the issue of those instructions, half of them the inverse's.  ABC as in
 // k_integrate: the general slot loops issue each of the 36 slot pairs of a
 // reaction under its own mask where A + B <=> C has nine.  Value and gradient,
-// general -> ABC: 21 species, 4,096 cells 30.2 -> 29.1 ms, 256 cells 10.7 -> 10.0;
-// 53 species, 512 cells 45.7 -> 43.2.
+// general -> ABC -> with the next step's row loaded ahead and its coefficients by
+// lane (adjoint_steps): 21 species, 4,096 cells 30.2 -> 29.1 -> 28.4 ms, 256 cells
+// 10.7 -> 10.0 -> 9.8; 53 species, 512 cells 45.7 -> 43.2 -> 42.5.
 // Waves per SIMD the adjoint kernels' registers must allow (1: compiler's
 // choice).  At 21 species the tiled elimination takes 100 to 110 registers, so
 // four; without a bound it took 153.
