@@ -232,9 +232,11 @@ __device__ __forceinline__ double pack_solve(const Lds &L, const Pack<G> &W, dou
 
 // Cells of the launch, G per wave (see the top of the file).  Isothermal
 // mechanisms, direct solver with the analytic Jacobian, no lock-step, no
-// checkpoints; full step records are kept.  Grid: persistent waves; a group
-// takes its cells from the work queue or, without one, every (groups of the
-// grid)-th cell of the list.  Blocks of at most 256 threads.
+// checkpoints; full step records are kept.  Grid: persistent waves whose groups
+// take their cells from the work queue, under every scheduler (the library's
+// static one has no order of cells to keep, and every (groups of the grid)-th cell
+// for a group leaves the groups with the long cells behind: 21 species, 262,144
+// cells 314 ms against 272).  Blocks of at most 256 threads.
 template <int S, typename LT, int MINW, int G, bool ABC>
 __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
   static_assert(S <= Pack<G>::kLanes, "a group holds one lane per species");
@@ -243,7 +245,6 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
   const int li = threadIdx.x & (kWave - 1);
   const Pack<G> W(li);
   const Grp<1> W1(li);
-  const int wpb = blockDim.x / kWave;
   constexpr int NL = Pack<G>::kLanes;
   const MechDev &m = P.mech;
   const int R = m.R;
@@ -291,8 +292,7 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
   const bool keep = P.rec != nullptr;
 
   // the group's share of the list
-  const int64_t n_groups = static_cast<int64_t>(gridDim.x) * wpb * G;
-  int64_t next = (static_cast<int64_t>(blockIdx.x) * wpb + wib) * G + W.grp, stop = 0;
+  int64_t next = 0, stop = 0;
   bool drained = false;
 
   bool live = false;  // the group has a cell
@@ -312,19 +312,17 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
   for (;;) {
     // ---- groups without a cell take one -------------------------------------
     if (!live && !drained) {
-      if (P.use_queue) {
-        if (next >= stop) {
-          unsigned int base = 0;
-          if (W.lane == 0) base = atomicAdd(P.queue, static_cast<unsigned int>(P.chunk));
-          next = static_cast<unsigned int>(W.from_lane0(static_cast<int>(base)));
-          stop = next + P.chunk;
-        }
+      if (next >= stop) {
+        unsigned int base = 0;
+        if (W.lane == 0) base = atomicAdd(P.queue, static_cast<unsigned int>(P.chunk));
+        next = static_cast<unsigned int>(W.from_lane0(static_cast<int>(base)));
+        stop = next + P.chunk;
       }
       if (next >= P.n_list) {
         drained = true;
       } else {
         cell = P.list ? P.list[next] : next;
-        next += P.use_queue ? 1 : n_groups;
+        ++next;
         live = true;
         // rate constants (Arrhenius, frozen T)
         const double T = P.T ? P.T[cell] : 1.0;
@@ -758,10 +756,12 @@ __host__ __device__ constexpr int packed_cells(int S) { return S <= 16 ? 4 : S <
 // leaves no SIMD without a wave and its steps are shorter.  Measured on 256
 // CUs, packed against one cell per wave, ms: 9 species 5.45 / 5.21 on 6,144
 // cells, 5.66 / 6.69 on 8,192, 43.4 / 74.7 on 131,072; 16 species 5.32 / 4.81 on
-// 6,144, 5.65 / 6.02 on 8,192; 3 species 2.73 / 2.67 on 8,192, 3.09 / 4.23 on
-// 16,384; 21 species FP64 13.7 / 12.9 on 8,192, 17.2 / 17.5 on 12,288, 71.7 /
+// 6,144, 5.65 / 6.02 on 8,192; 3 species 2.72 / 2.68 on 8,192, 2.90 / 3.40 on
+// 12,000; 21 species FP64 13.7 / 12.9 on 8,192, 17.2 / 17.5 on 12,288, 71.7 /
 // 80.0 on 65,536, FP32 matrix 16.6 / 16.2 on 12,288, 68.0 / 74.7 on 65,536.
-__host__ __device__ constexpr int packed_min_cells_per_cu(int S) { return S <= 16 ? 32 : 64; }
+__host__ __device__ constexpr int packed_min_cells_per_cu(int S) {
+  return S <= 4 ? 40 : S <= 16 ? 32 : 64;
+}
 
 // Waves per SIMD the packed kernel's registers must allow.  At 21 species FP64
 // the LDS holds 13 waves on a CU, so three (four spilled: 72.8 against 70.5 ms);

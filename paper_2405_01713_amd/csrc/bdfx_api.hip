@@ -936,8 +936,11 @@ int bdfx_integrate(bdfx_ctx ctx, double t0, double t_out) {
   HIPCHK(ctx, hipSetDevice(ctx->device));
   const bool fp32 = ctx->opt.lu_precision == 32;
   const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
-  if (queue) HIPCHK(ctx, bdfx_launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->ws + ctx->off_queue),
-                                              64, 0u, ctx->stream));
+  bool packed = false;  // packed launches pop cells under every scheduler
+  for (const Bin &b : ctx->bins) packed |= b.packed > 1;
+  if (queue || packed)
+    HIPCHK(ctx, bdfx_launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->ws + ctx->off_queue),
+                                     64, 0u, ctx->stream));
   if (ctx->pair) {
     const Bin &a = ctx->bins[ctx->pair_a], &b = ctx->bins[ctx->pair_b];
     bdfx::Params PA = make_params(ctx, a, t0, t_out), PB = make_params(ctx, b, t0, t_out);
@@ -1110,7 +1113,8 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
             e = bdfx_launch_copy_rows(ctx->y, ctx->ldy, P.list, trial.count, m->n, save, false,
                                       ctx->stream);
             if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-            if (e == hipSuccess && queue) e = bdfx_launch_fill_u32(qctr, 64, 0u, ctx->stream);
+            if (e == hipSuccess && (queue || trial.packed > 1))
+              e = bdfx_launch_fill_u32(qctr, 64, 0u, ctx->stream);
             if (e == hipSuccess) e = launch_bin(ctx, trial, P);
             if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
             if (e == hipSuccess)

@@ -22,11 +22,11 @@ def _run(w, y0, **opts):
 
 
 def _cells(S, extra):
-    """Cells that the library packs (32 a CU up to 16 species, 64 above), and
-    ``extra`` more so that the last wave is partly filled."""
+    """Cells that the library packs (40 a CU up to 4 species, 32 up to 16, 64
+    above), and ``extra`` more so that the last wave is partly filled."""
     import torch
     cu = torch.cuda.get_device_properties(0).multi_processor_count
-    return (32 if S <= 16 else 64) * cu + extra
+    return (40 if S <= 4 else 32 if S <= 16 else 64) * cu + extra
 
 
 @pytest.mark.parametrize("S,R,lu,sched", [(2, 3, 64, 1), (9, 30, 64, 0), (9, 30, 32, 1),
