@@ -97,7 +97,9 @@ typedef struct {
 } bdfx_mech_desc;
 
 /* Scheduler for bdfx_options.scheduler */
-#define BDFX_SCHED_STATIC 0 /* one lane group per cell, grid covers every cell */
+#define BDFX_SCHED_STATIC 0 /* one lane group per cell, grid covers every cell (several cells
+                               per wave, see cells_per_wave, pop them from the work queue
+                               under every scheduler) */
 #define BDFX_SCHED_QUEUE 1  /* persistent waves pop cells from an atomic work queue */
 #define BDFX_SCHED_FUSED 2  /* as BDFX_SCHED_QUEUE, and a batch of two mechanisms runs in
                                one launch: each block holds waves for both, the larger
