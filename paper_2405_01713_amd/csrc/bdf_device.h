@@ -1522,7 +1522,9 @@ __device__ __forceinline__ int panel_step(LT (&a)[4], LT &q, int row, int k, int
     const uint64_t tie = __ballot(hi == hmax) & kLanes;
     p = static_cast<int>(__builtin_ctzll(tie | (1ull << 63)));
     zero_pivot = false;
-    if (__builtin_expect(__builtin_popcountll(tie) != 1, 0)) {
+    // (a lone maximum of 1 is the last unused row, or a denormal pivot: the low
+    // words tell a zero)
+    if (__builtin_expect(__builtin_popcountll(tie) != 1 || hmax == 1u, 0)) {
       const uint32_t lo = static_cast<uint32_t>(bits);
       const uint32_t lmax = W.template max_u32<(S + 15) / 16>(hi == hmax ? lo : 0u);
       p = static_cast<int>(__builtin_ctzll(__ballot(hi == hmax && lo == lmax) | (1ull << 63)));

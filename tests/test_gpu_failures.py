@@ -163,6 +163,38 @@ def test_singular_newton_matrix_in_a_large_kernel(oracle, lu):
     assert np.all(sto["status"] == -6) and np.all(sto["nsetups"] == 2)
     assert np.array_equal(yo, y0[:8])
 
+
+@pytest.mark.parametrize("lu", [64, 32])
+@pytest.mark.parametrize("S,packed", [(9, False), (17, False), (19, False), (21, False), (32, False),
+                                      (33, False), (53, False), (64, False), (9, True), (17, True),
+                                      (21, True)])
+def test_singular_newton_matrix_in_the_last_columns(oracle, S, packed, lu):
+    """The autocatalytic species at the last two indices, in either order: the
+    missing pivot is met at the last elimination step, where one row is left
+    and nothing ties with it -- at the first attempt (gamma = 2^-20) or, in the
+    other order, at the second one.  ``packed``: a batch large enough for the
+    kernels with several cells per wave."""
+    import torch
+    n = 16
+    if packed:
+        n += (32 if S <= 16 else 64) * torch.cuda.get_device_properties(0).multi_processor_count
+    t_out = 10.0 * 2.0 ** -20
+    y0 = np.zeros((n, S))
+    y0[:, :S - 2] = np.random.default_rng(S).uniform(0.1, 1.0, size=(n, S - 2))
+    ks = np.ones((n, 2))
+    ks[:, 0], ks[:, 1] = 2.0 ** 20, 2.0 ** 22
+    for a, b in ((S - 1, S - 2), (S - 2, S - 1)):
+        m = dict(_autocatalytic(), n_species=S, w=np.ones(S),
+                 reac=np.array([[a, -1, -1], [b, -1, -1]], dtype=np.int32),
+                 prod=np.array([[a, a, -1], [b, b, -1]], dtype=np.int32))
+        w = dict(mechs=[m], y0=y0, T=np.ones(n), kscale=ks, rtol=1e-6, atol=1e-10, t_out=t_out)
+        y, st = _gpu(w, lu_precision=lu)
+        yo, sto = oracle.integrate([m], y0[:4], 0.0, t_out, 1e-6, 1e-10, T=np.ones(4), kscale=ks[:4])
+        assert np.all(sto["status"] == -6) and np.all(sto["ncfn"] == 0)
+        for key in ("status", "nst", "nfe", "nni", "nsetups", "netf", "ncfn"):
+            assert np.all(st[key] == sto[key][0]), (a, b, key)
+        assert np.array_equal(y, y0)
+
 def test_record_capacity(oracle):
     """A cell that needs more accepted steps than the record holds fails with
     -10 at its last recorded step: the returned state is the record's last
