@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(LOCK ? kWave * kMaxBatch : 256, MINW) k_integr
       if (!P.use_queue) break;
       unsigned int base = 0;
       if (W.lane == 0) base = atomicAdd(P.queue, static_cast<unsigned int>(P.chunk));
-      next = W.from_lane0(static_cast<int>(base));
+      next = static_cast<unsigned int>(W.from_lane0(static_cast<int>(base)));
       stop = next + P.chunk;
     }
     if (next >= P.n_list) break;
@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_pair(Params PA, Params 
       if (next >= stop) {
         unsigned int base = 0;
         if (W.lane == 0) base = atomicAdd(PA.queue, static_cast<unsigned int>(PA.chunk));
-        next = W.from_lane0(static_cast<int>(base));
+        next = static_cast<unsigned int>(W.from_lane0(static_cast<int>(base)));
         stop = next + PA.chunk;
       }
       if (next >= PA.n_list) break;
@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_pair(Params PA, Params 
     if (next >= stop) {
       unsigned int base = 0;
       if (W.lane == 0) base = atomicAdd(PB.queue, static_cast<unsigned int>(PB.chunk));
-      next = W.from_lane0(static_cast<int>(base));
+      next = static_cast<unsigned int>(W.from_lane0(static_cast<int>(base)));
       stop = next + PB.chunk;
     }
     if (next >= PB.n_list) break;

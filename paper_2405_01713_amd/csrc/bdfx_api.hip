@@ -20,6 +20,7 @@
 #include "bdfx.h"
 #include "bdf_kernels.h"
 #include "bdf_packed.h"
+#include "launch_rules.h"
 
 BDFX_DECLARE_SIZE(3)
 BDFX_DECLARE_SIZE(4)
@@ -649,6 +650,11 @@ static hipError_t launch_bin(bdfx_ctx ctx, const Bin &b, bdfx::Params P) {
   const bool fp32 = ctx->opt.lu_precision == 32;
   const bdfx_mech m = ctx->mechs[b.mech];
   P.lds_doubles = b.lds_doubles;
+  // (packed launches pop under the static scheduler too, which knows no chunks)
+  const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
+  P.chunk = bdfx::pop_chunk(queue ? b.queue_chunk : 1, b.count,
+                            static_cast<int64_t>(b.cfg.grid) * (b.cfg.block / bdfx::kWave) *
+                                (b.packed > 1 ? b.packed : b.cells_per_wave));
   if (b.packed > 1) return b.se->launch_packed(P, fp32, m->abc, b.cfg, ctx->stream);
   return b.se->launch(P, fp32, b.budget, b.tab, b.cells_per_wave, kernel_flags(ctx, m), b.cfg,
                       ctx->stream);
@@ -853,6 +859,21 @@ static int configure_pair(bdfx_ctx ctx) {
   return BDFX_OK;
 }
 
+// Enqueues the one launch of both bins (PA, PB from make_params of the bins a and
+// b of ctx->pair_a and ctx->pair_b, or of samples of them).
+static hipError_t launch_pair(bdfx_ctx ctx, const Bin &a, const Bin &b, bdfx::Params PA,
+                              bdfx::Params PB) {
+  const int64_t waves = static_cast<int64_t>(ctx->pair_cfg.grid) * (ctx->pair_cfg.block / bdfx::kWave);
+  PA.use_queue = PB.use_queue = 1;
+  PA.lds_doubles = a.lds_doubles;
+  PB.lds_doubles = ctx->pair_lds_b;
+  PA.pair_waves = PB.pair_waves = ctx->pair_waves;
+  PA.chunk = bdfx::pop_chunk(a.queue_chunk, a.count, waves);
+  PB.chunk = bdfx::pop_chunk(b.queue_chunk, b.count, waves);
+  return ctx->pair->launch(PA, PB, ctx->opt.lu_precision == 32, a.waves_per_simd, a.tab, ctx->pair_cfg,
+                           ctx->stream);
+}
+
 // Kernel, LDS size and grid of every bin (called by bdfx_bind).
 static int configure_bins(bdfx_ctx ctx) {
   for (Bin &b : ctx->bins) {
@@ -906,7 +927,6 @@ static bdfx::Params make_params(bdfx_ctx ctx, const Bin &b, double t0, double to
   P.n_sp = m->n;
   P.gmres_maxl = ctx->opt.gmres_maxl;
   P.queue = reinterpret_cast<uint32_t *>(ctx->ws + ctx->off_queue) + b.mech;
-  P.chunk = b.queue_chunk;
   P.kk_slots = ctx->kk_slots ? reinterpret_cast<double *>(ctx->ws + ctx->off_kk) : nullptr;
   P.kk_nslots = ctx->kk_slots;
   if (ctx->opt.record_steps > 0) {
@@ -934,7 +954,6 @@ int bdfx_integrate(bdfx_ctx ctx, double t0, double t_out) {
   if (!(t_out > t0) || !std::isfinite(t0) || !std::isfinite(t_out))
     return fail(ctx, BDFX_EINVAL, "need finite t_out > t0");
   HIPCHK(ctx, hipSetDevice(ctx->device));
-  const bool fp32 = ctx->opt.lu_precision == 32;
   const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
   bool packed = false;  // packed launches pop cells under every scheduler
   for (const Bin &b : ctx->bins) packed |= b.packed > 1;
@@ -943,13 +962,7 @@ int bdfx_integrate(bdfx_ctx ctx, double t0, double t_out) {
                                      64, 0u, ctx->stream));
   if (ctx->pair) {
     const Bin &a = ctx->bins[ctx->pair_a], &b = ctx->bins[ctx->pair_b];
-    bdfx::Params PA = make_params(ctx, a, t0, t_out), PB = make_params(ctx, b, t0, t_out);
-    PA.use_queue = PB.use_queue = 1;
-    PA.lds_doubles = a.lds_doubles;
-    PB.lds_doubles = ctx->pair_lds_b;
-    PA.pair_waves = PB.pair_waves = ctx->pair_waves;
-    HIPCHK(ctx, ctx->pair->launch(PA, PB, fp32, a.waves_per_simd, a.tab, ctx->pair_cfg,
-                                  ctx->stream));
+    HIPCHK(ctx, launch_pair(ctx, a, b, make_params(ctx, a, t0, t_out), make_params(ctx, b, t0, t_out)));
     ctx->last_t0 = t0;
     ctx->last_tout = t_out;
     ctx->integrated = true;
@@ -1010,7 +1023,6 @@ static bdfx_tuning tuning_of(bdfx_ctx ctx, const Bin &b) {
 // other and the one-launch form (ctx->pair set); both in ms.
 static hipError_t time_pair(bdfx_ctx ctx, double t0, double t_out, int64_t ns, hipEvent_t e0,
                             hipEvent_t e1, float *t_seq, float *t_pair) {
-  const bool fp32 = ctx->opt.lu_precision == 32;
   const Bin *bin[2] = {&ctx->bins[ctx->pair_a], &ctx->bins[ctx->pair_b]};
   Bin tb[2];
   bdfx::Params P[2];
@@ -1020,8 +1032,6 @@ static hipError_t time_pair(bdfx_ctx ctx, double t0, double t_out, int64_t ns, h
     tb[k].count = std::min(ns, bin[k]->count);
     P[k] = make_params(ctx, tb[k], t0, t_out);
     P[k].use_queue = 1;
-    P[k].lds_doubles = bin[k]->lds_doubles;
-    P[k].chunk = bin[k]->queue_chunk;
     save[k] = reinterpret_cast<double *>(ctx->ws + ctx->off_tune) +
               static_cast<int64_t>(k) * ctx->tune_cells * ctx->S_max;
   }
@@ -1038,11 +1048,7 @@ static hipError_t time_pair(bdfx_ctx ctx, double t0, double t_out, int64_t ns, h
       if (form == 0) {
         for (int k = 0; k < 2 && e == hipSuccess; ++k) e = launch_bin(ctx, tb[k], P[k]);
       } else if (e == hipSuccess) {
-        bdfx::Params PA = P[0], PB = P[1];
-        PB.lds_doubles = ctx->pair_lds_b;
-        PA.pair_waves = PB.pair_waves = ctx->pair_waves;
-        e = ctx->pair->launch(PA, PB, fp32, tb[0].waves_per_simd, tb[0].tab, ctx->pair_cfg,
-                              ctx->stream);
+        e = launch_pair(ctx, tb[0], tb[1], P[0], P[1]);
       }
       if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
       for (int k = 0; k < 2 && e == hipSuccess; ++k)
@@ -1070,7 +1076,6 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
     for (size_t bi = 0; bi < ctx->bins.size() && out; ++bi) out[bi] = tuning_of(ctx, ctx->bins[bi]);
     return BDFX_OK;
   }
-  const bool fp32 = ctx->opt.lu_precision == 32;
   const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
   const int64_t ns = sample_cells > 0 ? std::min(sample_cells, ctx->tune_cells) : ctx->tune_cells;
   ctx->integrated = false;  // the timed runs overwrite the sample cells' step records
@@ -1106,7 +1111,6 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
           trial.waves_per_block = wpb;
           trial.queue_chunk = chunk;
           if (configure_bin(ctx, trial) != BDFX_OK) continue;  // e.g. LDS too large
-          P.chunk = chunk;
           float total = 0.0f;
           hipError_t e = hipSuccess;
           for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // rep 0 warms up

@@ -66,3 +66,26 @@ def test_packed_generic_slots_forcing_scale_and_records(oracle):
                                                 {0, -10} if "record_steps" in opts else {0})
         for a, b in zip(rec or [], rec1 or []):
             assert all(np.array_equal(a[key], b[key]) for key in a)
+
+
+@pytest.mark.parametrize("chunk", [64, 2 ** 31 - 1])
+def test_static_packed_launch_ignores_the_chunk(chunk):
+    """queue_chunk is the work-queue schedulers' option: a packed launch of the
+    static one, which takes its cells from the counter too, pops single cells."""
+    n = _cells(3, 1)
+    c = W.robertson_cells(n)
+    w = dict(mechs=[W.robertson_mechanism()], kscale=c["kscale"], t_out=1.0)
+    y, st, _ = _run(w, c["y0"])
+    y1, st1, _ = _run(w, c["y0"], queue_chunk=chunk)
+    assert np.all(st["status"] == 0)
+    assert np.array_equal(st, st1) and np.array_equal(y, y1)
+
+
+def test_largest_chunk_hands_out_every_cell_once():
+    """A chunk for which the 32-bit counter would wrap (64 waves that each pop
+    2^31 - 1 cells) is bounded by the library."""
+    c = W.robertson_cells(64)
+    w = dict(mechs=[W.robertson_mechanism()], kscale=c["kscale"], t_out=1.0)
+    y, st, _ = _run(w, c["y0"], scheduler=1)
+    y1, st1, _ = _run(w, c["y0"], scheduler=1, queue_chunk=2 ** 31 - 1)
+    assert np.array_equal(st, st1) and np.array_equal(y, y1)

@@ -1,0 +1,43 @@
+"""The launch code's choices (csrc/launch_rules.h), compiled for the host."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+_SRC = r"""
+#include "launch_rules.h"
+extern "C" {
+int32_t pop_chunk(int32_t a, int64_t c, int64_t p) { return bdfx::pop_chunk(a, c, p); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, so = str(d / "rules.cpp"), str(d / "rules.so")
+    with open(src, "w") as fh:
+        fh.write(_SRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2405_01713_amd", "csrc"), src, "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.pop_chunk.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64]
+    return lib
+
+
+@pytest.mark.parametrize("cells,poppers", [(1, 1), (64, 64), (8195, 16384), (131072, 16384),
+                                           (2 ** 20, 8192), (2 ** 31 - 1, 16384),
+                                           (2 ** 31 - 1, 1)])
+@pytest.mark.parametrize("asked", [1, 4, 64, 2 ** 18, 2 ** 20, 2 ** 31 - 1])
+def test_the_queue_counter_never_wraps(rules, asked, cells, poppers):
+    """Every lane group pops once more than there are cells for it; the counter
+    has to stay below 2^32 whatever chunk the options ask for."""
+    chunk = rules.pop_chunk(asked, cells, poppers)
+    assert 1 <= chunk <= asked
+    assert (-(-cells // chunk) + poppers) * chunk < 2 ** 32
+    # an ordinary request is taken as it is
+    if (-(-cells // asked) + poppers + 1) * asked < 2 ** 32:
+        assert chunk == asked
