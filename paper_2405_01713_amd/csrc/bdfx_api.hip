@@ -613,7 +613,8 @@ int bdfx_bind(bdfx_ctx ctx, void *d_ws, size_t ws_bytes, double *d_y, int32_t ld
 // depend on it.
 static int packed_cells_of(bdfx_ctx ctx, const Bin &b) {
   const bdfx_mech m = ctx->mechs[b.mech];
-  if (!b.se->launch_packed || b.cells_per_wave != 1 || b.waves_per_simd != 0 || m->thermal ||
+  if (!b.se->launch_packed || b.cells_per_wave != 1 || b.waves_per_simd != 0 ||
+      b.waves_per_block > 4 || m->thermal ||
       lin_of(ctx) != bdfx::kLinAnalytic || ctx->opt.lockstep > 0 || ctx->opt.checkpoint_every > 0 ||
       b.count < static_cast<int64_t>(bdfx::packed_min_cells_per_cu(b.se->S)) * ctx->n_cu)
     return 1;
@@ -624,7 +625,7 @@ static int packed_cells_of(bdfx_ctx ctx, const Bin &b) {
 static int configure_packed(bdfx_ctx ctx, Bin &b) {
   const bool fp32 = ctx->opt.lu_precision == 32;
   const bdfx_mech m = ctx->mechs[b.mech];
-  const int waves = std::min(std::max(b.waves_per_block, 1), 4);
+  const int waves = std::max(b.waves_per_block, 1);
   b.cfg.block = bdfx::kWave * waves;
   b.lds_doubles = b.packed == 4 ? bdfx::PackLds<4>::size(b.se->S, m->R, fp32 ? 4 : 8)
                                 : bdfx::PackLds<2>::size(b.se->S, m->R, fp32 ? 4 : 8);
@@ -638,10 +639,10 @@ static int configure_packed(bdfx_ctx ctx, Bin &b) {
     b.packed = 1;
     return BDFX_OK;
   }
-  const int per_cu = ctx->opt.blocks_per_cu > 0 ? ctx->opt.blocks_per_cu : occ;
-  const int64_t per_block = static_cast<int64_t>(waves) * b.packed;
-  b.cfg.grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(per_cu) * ctx->n_cu,
-                                                  (b.count + per_block - 1) / per_block));
+  // (blocks_per_cu is the persistent schedulers' option)
+  const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
+  b.cfg.grid = bdfx::persistent_grid(queue ? ctx->opt.blocks_per_cu : 0, occ, ctx->n_cu, b.count,
+                                     static_cast<int64_t>(waves) * b.packed);
   return BDFX_OK;
 }
 
@@ -762,8 +763,7 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
     HIPCHK(ctx, b.se->occupancy(fp32, b.budget, k, cpw, kernel_flags(ctx, m), b.cfg.block, lds[k],
                                 &occ[k]));
     if (queue) {
-      const int per_cu = ctx->opt.blocks_per_cu > 0 ? ctx->opt.blocks_per_cu : std::max(occ[k], 1);
-      grid[k] = std::min<int64_t>(static_cast<int64_t>(per_cu) * ctx->n_cu, need);
+      grid[k] = bdfx::persistent_grid(ctx->opt.blocks_per_cu, occ[k], ctx->n_cu, b.count, per_block);
     }
     if (k == bdfx::kTabGlobal && grid[k] * waves > ctx->kk_slots) occ[k] = 0;
   }

@@ -18,4 +18,11 @@ inline int32_t pop_chunk(int32_t asked, int64_t cells, int64_t poppers) {
   return static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(asked, most)));
 }
 
+// Blocks of a persistent grid: `asked` per CU (0: as many as reside), and no more
+// than the cells fill.
+inline int32_t persistent_grid(int32_t asked, int resident, int n_cu, int64_t cells, int64_t per_block) {
+  const int64_t per_cu = asked > 0 ? asked : std::max(resident, 1);
+  return static_cast<int32_t>(std::min(per_cu * n_cu, (cells + per_block - 1) / per_block));
+}
+
 }  // namespace bdfx

@@ -89,3 +89,29 @@ def test_largest_chunk_hands_out_every_cell_once():
     y, st, _ = _run(w, c["y0"], scheduler=1)
     y1, st1, _ = _run(w, c["y0"], scheduler=1, queue_chunk=2 ** 31 - 1)
     assert np.array_equal(st, st1) and np.array_equal(y, y1)
+
+
+def test_static_packed_launch_ignores_blocks_per_cu():
+    """blocks_per_cu is the persistent schedulers' option; under the static one
+    the cells keep all of the GPU (one block a CU would hold a tenth of them:
+    several times the time)."""
+    import time
+
+    import torch
+    from paper_2405_01713_amd import bdfx
+    n = _cells(3, 1)
+    c = W.robertson_cells(n)
+    best = []
+    for opts in (dict(), dict(blocks_per_cu=1)):
+        integ = bdfx.Integrator([W.robertson_mechanism()], c["y0"], 1e-6, 1e-10, kscale=c["kscale"], **opts)
+        ms = []
+        for _ in range(4):
+            integ.set_state(c["y0"])
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            integ.integrate(0.0, 40.0)
+            torch.cuda.synchronize()
+            ms.append(time.perf_counter() - t)
+        best.append(min(ms))
+        integ.close()
+    assert best[1] < 2.0 * best[0], best

@@ -11,6 +11,9 @@ _SRC = r"""
 #include "launch_rules.h"
 extern "C" {
 int32_t pop_chunk(int32_t a, int64_t c, int64_t p) { return bdfx::pop_chunk(a, c, p); }
+int32_t persistent_grid(int32_t a, int r, int n, int64_t c, int64_t b) {
+  return bdfx::persistent_grid(a, r, n, c, b);
+}
 }
 """
 
@@ -25,6 +28,8 @@ def rules(tmp_path_factory):
                     os.path.join(ROOT, "paper_2405_01713_amd", "csrc"), src, "-o", so], check=True)
     lib = ctypes.CDLL(so)
     lib.pop_chunk.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64]
+    lib.persistent_grid.argtypes = [ctypes.c_int32, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
+                                    ctypes.c_int64]
     return lib
 
 
@@ -41,3 +46,13 @@ def test_the_queue_counter_never_wraps(rules, asked, cells, poppers):
     # an ordinary request is taken as it is
     if (-(-cells // asked) + poppers + 1) * asked < 2 ** 32:
         assert chunk == asked
+
+
+def test_persistent_grid(rules):
+    g = rules.persistent_grid
+    assert g(0, 4, 256, 10 ** 6, 16) == 1024  # as many blocks as reside
+    assert g(0, 0, 256, 10 ** 6, 16) == 256  # at least one a CU
+    assert g(2, 4, 256, 10 ** 6, 16) == 512  # as many as asked for
+    assert g(0, 4, 256, 1001, 16) == 63  # no more than the cells fill
+    assert g(2 ** 31 - 1, 4, 256, 2 ** 31 - 1, 1) == 2 ** 31 - 1
+    assert g(0, 4, 256, 0, 16) == 0
