@@ -240,8 +240,11 @@ const void *by_budget(int w) {
   constexpr bool kBig = S > 32 && LIN != kLinGmres;
   constexpr int CAP = kBig ? (sizeof(LT) == 8 ? 2 : 3) : 5;
   // budget 0, the compiler's choice: bounded where the elimination would take
-  // more registers than leave the waves the LDS has room for
-  constexpr int W0 = kBig ? CAP : S > 16 && LIN != kLinGmres ? 3 : 1;
+  // more registers than leave the waves the LDS has room for.  Not with two cells
+  // per wave, whose row form spills under it, ms bounded / not: FP64, 30 species
+  // 55.9 / 50.1 on 8,192 cells, 184 / 166 on 32,768, 21 species 11.0 / 10.1 on
+  // 2,048, 67.2 / 68.3 on 32,768; FP32, 30 species 31.6 / 30.5 on 8,192.
+  constexpr int W0 = kBig ? CAP : G == 1 && S > 16 && LIN != kLinGmres ? 3 : 1;
   constexpr int W3 = CAP < 3 ? CAP : 3, W4 = CAP < 4 ? CAP : 4, W5 = CAP;
   static const F t[4] = {F(&k_integrate<S, LT, W0, TAB, G, ABC, TH, LIN>),
                          F(&k_integrate<S, LT, W3, TAB, G, ABC, TH, LIN>),
