@@ -11,6 +11,18 @@
 
 namespace bdfx {
 
+// Threads of the largest lock-step block.  Above 32 species the matrix tiles
+// alone take up to 128 registers, all that blocks of 16 waves would leave a
+// lane, while the LDS of a block (64 KiB) holds few waves: 2 at 53 species in
+// FP64, 5 in FP32, 1 and 3 at 64.  (Every wave has at least one reaction's tables.)
+// Blocks of 16 waves -> these, ms for 4,096 cells: 53 species FP64 60.7 -> 39.7 in
+// batches of 1, 65.4 -> 42.8 of 2 (rows in lanes under 128 registers: 55.3, 60.5);
+// FP32 29.0 -> 26.3 of 1; 60 species FP64 89.8 -> 41.8, FP32 31.2 -> 25.3.
+__host__ __device__ constexpr int lock_threads(int S, int lt_bytes) {
+  const int fit = (65536 - (2 * kMaxBatch + 2) * 8) / (8 * lds_doubles(S, 1, lt_bytes));
+  return kWave * (S <= 32 || fit > kMaxBatch ? kMaxBatch : fit);
+}
+
 // MINW: minimum resident waves per SIMD the register allocation must allow
 // (1 = compiler's choice; 3 = at most 168 VGPRs, 4 = at most 128, 5 = at
 // most 96, spilling if needed).  TAB: placement of the reaction tables
@@ -29,7 +41,7 @@ namespace bdfx {
 // hands out batches.  Blocks of up to kMaxBatch waves.
 template <int S, typename LT, int MINW, int TAB, int G, bool ABC, bool TH,
           int LIN = kLinAnalytic, bool LOCK = false>
-__global__ void __launch_bounds__(LOCK ? kWave * kMaxBatch : 256, MINW) k_integrate(Params P) {
+__global__ void __launch_bounds__(LOCK ? lock_threads(S, sizeof(LT)) : 256, MINW) k_integrate(Params P) {
   extern __shared__ double smem[];
   // (a scalar LDS base; the non-isothermal kernels keep the form in which their
   // energy sums are fused as they always were: with it the last bits moved)
@@ -218,18 +230,20 @@ const void *adjoint_kernel(int kind, bool abc) {
   return abc ? (const void *)&k_adj_rerun<S, true> : (const void *)&k_adj_rerun<S, false>;
 }
 
-// the three register budgets of one kernel configuration
-// lock-step kernels: one register budget (the block of up to 16 waves caps
-// the registers anyway), one cell per wave, tables in LDS
+// lock-step kernels: one register budget, one cell per wave, tables in LDS
 template <int S>
 const void *lock_kernel(bool fp32, bool abc) {
+  // (above 32 species as many waves per SIMD as in by_budget; below, the block of
+  // up to 16 waves bounds the registers)
+  constexpr int W8 = S > 32 ? 2 : 1, W4 = S > 32 ? 3 : 1;
   if (abc)
-    return fp32 ? (const void *)&k_integrate<S, float, 1, kTabLds, 1, true, false, kLinAnalytic, true>
-                : (const void *)&k_integrate<S, double, 1, kTabLds, 1, true, false, kLinAnalytic, true>;
-  return fp32 ? (const void *)&k_integrate<S, float, 1, kTabLds, 1, false, false, kLinAnalytic, true>
-              : (const void *)&k_integrate<S, double, 1, kTabLds, 1, false, false, kLinAnalytic, true>;
+    return fp32 ? (const void *)&k_integrate<S, float, W4, kTabLds, 1, true, false, kLinAnalytic, true>
+                : (const void *)&k_integrate<S, double, W8, kTabLds, 1, true, false, kLinAnalytic, true>;
+  return fp32 ? (const void *)&k_integrate<S, float, W4, kTabLds, 1, false, false, kLinAnalytic, true>
+              : (const void *)&k_integrate<S, double, W8, kTabLds, 1, false, false, kLinAnalytic, true>;
 }
 
+// the register budgets of one kernel configuration
 template <int S, typename LT, int TAB, int G, bool ABC, bool TH = false, int LIN = kLinAnalytic>
 const void *by_budget(int w) {
   using F = const void *;

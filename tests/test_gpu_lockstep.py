@@ -162,3 +162,21 @@ def test_lockstep_largest_batch_small_system(oracle, parity):
     nst = st["nst"]
     for k in range(0, 100, 16):
         assert np.all(nst[k:k + 16] == nst[k])
+
+
+@pytest.mark.parametrize("S,R,B,lu", [(33, 120, 2, 64), (53, 325, 1, 64), (53, 325, 2, 64),
+                                      (53, 11, 5, 32), (53, 325, 3, 32), (60, 200, 1, 64),
+                                      (64, 150, 1, 64), (64, 60, 3, 32)])
+def test_lockstep_above_32_species(oracle, parity, S, R, B, lu):
+    """Batches up to the largest that the LDS of a block holds (the kernels'
+    blocks are bounded by it), the last one short."""
+    m = W.synthetic_mechanism(S, R, 5)
+    n = 12 * B - (B > 1)
+    c = W.cell_states(m, n, seed=S)
+    w = dict(mechs=[m], y0=c["y0"], T=c["T"], rtol=1e-6, atol=1e-10, t_out=1e-7)
+    y, st = _gpu(w, lockstep=B, lu_precision=lu)
+    yo, sto = _oracle(oracle, w, B)
+    assert np.all(st["status"] == 0) and np.all(sto["status"] == 0)
+    # one batch of the twelve may follow another valid step sequence (conftest)
+    parity(y, yo, w, f"S={S} B{B} LU{lu}", min_frac=0.9)
+    assert abs(st["nst"].mean() / sto["nst"].mean() - 1.0) < 0.06
