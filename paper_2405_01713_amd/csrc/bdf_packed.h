@@ -6,10 +6,11 @@
 // per group of 64 / G lanes (lane i of a group owns species i): the vector work
 // of one step, and the scalar work that is bound to it, is issued once for G
 // cells.  The kernels are bound by VALU issue (77 to 85 % busy at 4 or 5 waves per
-// SIMD), so that is where the time goes.  One cell per wave -> packed: 9 species,
-// 131,072 cells 74.7 -> 43.4 ms; 3 species, 65,536 cells 14.7 -> 8.3 ms; 21
-// species, 262,144 cells 333 -> 271 ms.  What is left is above all the setups
-// (55 % of the instructions at 21 species, 42 % at 9), which run a cell at a time.
+// SIMD), so that is where the time goes.  One cell per wave -> packed, ms (the
+// same build, 5-wave budget): 9 species, 131,072 cells 69.6 -> 43.3; 3 species,
+// 65,536 cells 13.3 -> 8.3; 16 species, 65,536 cells 44.5 -> 37.5; 21 species
+// FP32, 262,144 cells 275 -> 257.  What is left is above all the setups (42 % of
+// the instructions at 9 species), which run a cell at a time.
 //
 // Two things make the groups worth their divergence.  The loop runs over step
 // *attempts*, not over cells: a group whose cell is finished writes it and takes
@@ -235,8 +236,8 @@ __device__ __forceinline__ double pack_solve(const Lds &L, const Pack<G> &W, dou
 // checkpoints; full step records are kept.  Grid: persistent waves whose groups
 // take their cells from the work queue, under every scheduler (the library's
 // static one has no order of cells to keep, and every (groups of the grid)-th cell
-// for a group leaves the groups with the long cells behind: 21 species, 262,144
-// cells 314 ms against 272).  Blocks of at most 256 threads.
+// for a group leaves the groups with the long cells behind: 9 species, 20,011
+// cells 9.9 ms against 9.0).  Blocks of at most 256 threads.
 template <int S, typename LT, int MINW, int G, bool ABC>
 __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
   static_assert(S <= Pack<G>::kLanes, "a group holds one lane per species");
@@ -752,34 +753,22 @@ __global__ void __launch_bounds__(256, MINW) k_integrate_packed(Params P) {
 // on a CU than one (16,384 cells of 30 species: 46.8 ms against 36.6).
 __host__ __device__ constexpr int packed_cells(int S) { return S <= 16 ? 4 : S <= 21 ? 2 : 1; }
 
-// Cells per CU from which a launch is packed.  With fewer, one cell per wave
-// leaves no SIMD without a wave and its steps are shorter.  Measured on 256
-// CUs, packed against one cell per wave, ms: 9 species 5.45 / 5.21 on 6,144
-// cells, 5.66 / 6.69 on 8,192, 43.4 / 74.7 on 131,072; 16 species 5.32 / 4.81 on
-// 6,144, 5.65 / 6.02 on 8,192; 3 species 2.72 / 2.68 on 8,192, 2.90 / 3.40 on
-// 12,000; 21 species FP64 13.7 / 12.9 on 8,192, 17.2 / 17.5 on 12,288, 71.7 /
-// 80.0 on 65,536, FP32 matrix 16.6 / 16.2 on 12,288, 68.0 / 74.7 on 65,536.
-__host__ __device__ constexpr int packed_min_cells_per_cu(int S) {
-  return S <= 4 ? 40 : S <= 16 ? 32 : 64;
-}
+// Waves per SIMD the packed kernel's registers must allow.  (Up to 16 species five
+// spilled 120 bytes per lane for no gain below 100,000 cells.)
+constexpr int kPackedWaves = 4;
 
-// Waves per SIMD the packed kernel's registers must allow.  At 21 species FP64
-// the LDS holds 13 waves on a CU, so three (four spilled: 72.8 against 70.5 ms);
-// up to 16 species five spilled 120 bytes per lane for no gain below 100,000
-// cells.
-template <typename LT>
-__host__ __device__ constexpr int packed_waves(int S) {
-  return S <= 16 ? 4 : sizeof(LT) == 8 ? 3 : 4;
-}
-
+// nullptr: not built (17 to 21 species with the FP64 matrix, where one cell per
+// wave is as fast, see packed_min_cells_per_cu)
 template <int S>
 const void *packed_kernel(bool fp32, bool abc) {
-  constexpr int G = packed_cells(S), W8 = packed_waves<double>(S), W4 = packed_waves<float>(S);
-  if (abc)
-    return fp32 ? (const void *)&k_integrate_packed<S, float, W4, G, true>
-                : (const void *)&k_integrate_packed<S, double, W8, G, true>;
-  return fp32 ? (const void *)&k_integrate_packed<S, float, W4, G, false>
-              : (const void *)&k_integrate_packed<S, double, W8, G, false>;
+  constexpr int G = packed_cells(S), W = kPackedWaves;
+  if (fp32)
+    return abc ? (const void *)&k_integrate_packed<S, float, W, G, true>
+               : (const void *)&k_integrate_packed<S, float, W, G, false>;
+  if constexpr (S <= 16)
+    return abc ? (const void *)&k_integrate_packed<S, double, W, G, true>
+               : (const void *)&k_integrate_packed<S, double, W, G, false>;
+  return nullptr;
 }
 
 }  // namespace bdfx
@@ -792,12 +781,14 @@ const void *packed_kernel(bool fp32, bool abc) {
 #define BDFX_DEFINE_PACKED(S)                                                                    \
   hipError_t bdfx_launch_packed_s##S(const bdfx::Params &P, bool fp32, bool abc,                 \
                                      const bdfx::LaunchCfg &c, hipStream_t s) {                  \
+    const void *f = bdfx::packed_kernel<S>(fp32, abc);                                           \
+    if (!f) return hipErrorInvalidDeviceFunction;                                                \
     bdfx::Params arg = P;                                                                        \
     void *args[] = {&arg};                                                                       \
-    return hipLaunchKernel(bdfx::packed_kernel<S>(fp32, abc), dim3(c.grid), dim3(c.block), args, \
-                           c.lds_bytes, s);                                                      \
+    return hipLaunchKernel(f, dim3(c.grid), dim3(c.block), args, c.lds_bytes, s);                \
   }                                                                                              \
   hipError_t bdfx_occupancy_packed_s##S(bool fp32, bool abc, int block, size_t lds, int *out) {  \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(out, bdfx::packed_kernel<S>(fp32, abc),  \
-                                                        block, lds);                             \
+    const void *f = bdfx::packed_kernel<S>(fp32, abc);                                           \
+    *out = 0;                                                                                    \
+    return f ? hipOccupancyMaxActiveBlocksPerMultiprocessor(out, f, block, lds) : hipSuccess;    \
   }

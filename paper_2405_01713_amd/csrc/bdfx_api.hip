@@ -607,42 +607,36 @@ int bdfx_bind(bdfx_ctx ctx, void *d_ws, size_t ws_bytes, double *d_y, int32_t ld
 // integrate
 // ---------------------------------------------------------------------------
 
-// Cells per wave of this bin's launch under the library's own choice of shape
-// (waves_per_simd 0, one cell per wave asked for): the packed kernel's count
-// where it applies and the cells are enough for it, else 1.  Results do not
-// depend on it.
-static int packed_cells_of(bdfx_ctx ctx, const Bin &b) {
-  const bdfx_mech m = ctx->mechs[b.mech];
-  if (!b.se->launch_packed || b.cells_per_wave != 1 || b.waves_per_simd != 0 ||
-      b.waves_per_block > 4 || m->thermal ||
-      lin_of(ctx) != bdfx::kLinAnalytic || ctx->opt.lockstep > 0 || ctx->opt.checkpoint_every > 0 ||
-      b.count < static_cast<int64_t>(bdfx::packed_min_cells_per_cu(b.se->S)) * ctx->n_cu)
-    return 1;
-  return bdfx::packed_cells(b.se->S);
-}
-
-// Launch of the packed kernel: persistent waves, as many as are resident.
+// Launch of several cells per wave: persistent waves, as many as are resident.
+// Taken under the library's own choice of shape (waves_per_simd 0, one cell per
+// wave asked for) where a packed kernel applies and the cells are enough for it
+// (b.packed > 1); else b.packed is 1.  Results do not depend on it.
 static int configure_packed(bdfx_ctx ctx, Bin &b) {
   const bool fp32 = ctx->opt.lu_precision == 32;
   const bdfx_mech m = ctx->mechs[b.mech];
-  const int waves = std::max(b.waves_per_block, 1);
-  b.cfg.block = bdfx::kWave * waves;
-  b.lds_doubles = b.packed == 4 ? bdfx::PackLds<4>::size(b.se->S, m->R, fp32 ? 4 : 8)
-                                : bdfx::PackLds<2>::size(b.se->S, m->R, fp32 ? 4 : 8);
-  b.cfg.lds_bytes = (static_cast<size_t>(waves) * b.packed * b.lds_doubles +
-                     bdfx::PackHead::size(m->R)) * 8;
-  b.tab = bdfx::kTabLds;
-  int occ = 0;
-  if (b.cfg.lds_bytes <= 65536)
-    HIPCHK(ctx, b.se->occupancy_packed(fp32, m->abc, b.cfg.block, b.cfg.lds_bytes, &occ));
-  if (occ < 1) {  // a mechanism whose areas do not fit: one cell per wave
-    b.packed = 1;
+  b.packed = 1;
+  if (!b.se->launch_packed || b.cells_per_wave != 1 || b.waves_per_simd != 0 ||
+      b.waves_per_block > 4 || m->thermal || lin_of(ctx) != bdfx::kLinAnalytic ||
+      ctx->opt.lockstep > 0 || ctx->opt.checkpoint_every > 0)
     return BDFX_OK;
-  }
+  const int waves = std::max(b.waves_per_block, 1), cells = bdfx::packed_cells(b.se->S);
+  const int32_t d = cells == 4 ? bdfx::PackLds<4>::size(b.se->S, m->R, fp32 ? 4 : 8)
+                               : bdfx::PackLds<2>::size(b.se->S, m->R, fp32 ? 4 : 8);
+  const size_t lds = (static_cast<size_t>(waves) * cells * d + bdfx::PackHead::size(m->R)) * 8;
+  if (lds > 65536) return BDFX_OK;
+  int occ = 0;
+  HIPCHK(ctx, b.se->occupancy_packed(fp32, m->abc, bdfx::kWave * waves, lds, &occ));
+  const int64_t least = bdfx::packed_min_cells_per_cu(b.se->S, m->R, fp32, occ * waves);
+  if (occ < 1 || least == 0 || b.count < least * ctx->n_cu) return BDFX_OK;
+  b.packed = cells;
+  b.lds_doubles = d;
+  b.tab = bdfx::kTabLds;
+  b.cfg.block = bdfx::kWave * waves;
+  b.cfg.lds_bytes = lds;
   // (blocks_per_cu is the persistent schedulers' option)
   const bool queue = ctx->opt.scheduler != BDFX_SCHED_STATIC;
   b.cfg.grid = bdfx::persistent_grid(queue ? ctx->opt.blocks_per_cu : 0, occ, ctx->n_cu, b.count,
-                                     static_cast<int64_t>(waves) * b.packed);
+                                     static_cast<int64_t>(waves) * cells);
   return BDFX_OK;
 }
 
@@ -725,11 +719,8 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
   // lock-step: one block per batch, one wave per cell of it, tables in LDS,
   // and the batch's reduction slots after the waves' areas
   const int lock = ctx->opt.lockstep;
-  b.packed = packed_cells_of(ctx, b);
-  if (b.packed > 1) {
-    const int rc = configure_packed(ctx, b);
-    if (rc || b.packed > 1) return rc;
-  }
+  if (const int rc = configure_packed(ctx, b)) return rc;
+  if (b.packed > 1) return BDFX_OK;
   if (lock > 0) {  // the one shape of the lock-step kernels, as reported by bdfx_get_tuning
     b.waves_per_block = lock;
     b.waves_per_simd = 0;

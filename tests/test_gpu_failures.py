@@ -173,11 +173,11 @@ def test_singular_newton_matrix_in_the_last_columns(oracle, S, packed, lu):
     missing pivot is met at the last elimination step, where one row is left
     and nothing ties with it -- at the first attempt (gamma = 2^-20) or, in the
     other order, at the second one.  ``packed``: a batch large enough for the
-    kernels with several cells per wave."""
+    kernels with several cells per wave (FP32 above 16 species)."""
     import torch
     n = 16
     if packed:
-        n += (32 if S <= 16 else 64) * torch.cuda.get_device_properties(0).multi_processor_count
+        n += (32 if S <= 16 else 96) * torch.cuda.get_device_properties(0).multi_processor_count
     t_out = 10.0 * 2.0 ** -20
     y0 = np.zeros((n, S))
     y0[:, :S - 2] = np.random.default_rng(S).uniform(0.1, 1.0, size=(n, S - 2))

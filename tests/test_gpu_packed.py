@@ -115,3 +115,22 @@ def test_static_packed_launch_ignores_blocks_per_cu():
         best.append(min(ms))
         integ.close()
     assert best[1] < 2.0 * best[0], best
+
+
+@pytest.mark.parametrize("S,R,lu,sched,per_cu", [(9, 64, 64, 1, 48), (12, 70, 64, 1, 128), (14, 48, 32, 0, 32),
+                                                 (16, 64, 64, 1, 48), (16, 65, 32, 1, 48),
+                                                 (17, 30, 32, 1, 96), (21, 84, 32, 0, 96),
+                                                 (21, 110, 32, 1, 96)])
+def test_packed_from_the_cells_that_the_reactions_ask_for(S, R, lu, sched, per_cu):
+    """As above at the counts from which mechanisms of more reactions are packed."""
+    import torch
+    m = W.synthetic_mechanism(S, R, 1)
+    n = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + 3
+    c = W.cell_states(m, n, seed=11)
+    y0 = c["y0"]
+    y0[7, 0] = np.nan  # a failing cell among the others
+    w = dict(mechs=[m], T=c["T"], t_out=1e-8)
+    y, st, _ = _run(w, y0, lu_precision=lu, scheduler=sched)
+    y1, st1, _ = _run(w, y0, lu_precision=lu, scheduler=sched, waves_per_simd=3)
+    assert st["status"][7] == -9 and np.all(np.delete(st["status"], 7) == 0)
+    assert np.array_equal(st, st1) and np.array_equal(y, y1, equal_nan=True)

@@ -14,6 +14,9 @@ int32_t pop_chunk(int32_t a, int64_t c, int64_t p) { return bdfx::pop_chunk(a, c
 int32_t persistent_grid(int32_t a, int r, int n, int64_t c, int64_t b) {
   return bdfx::persistent_grid(a, r, n, c, b);
 }
+int packed_min_cells_per_cu(int S, int R, int fp32, int waves) {
+  return bdfx::packed_min_cells_per_cu(S, R, fp32 != 0, waves);
+}
 }
 """
 
@@ -56,3 +59,19 @@ def test_persistent_grid(rules):
     assert g(0, 4, 256, 1001, 16) == 63  # no more than the cells fill
     assert g(2 ** 31 - 1, 4, 256, 2 ** 31 - 1, 1) == 2 ** 31 - 1
     assert g(0, 4, 256, 0, 16) == 0
+
+
+def test_packing_looks_at_reactions_and_resident_waves(rules):
+    """The measured pairs at which one cell per wave is faster are not packed,
+    those at which packing is faster are (cells per CU 0: never)."""
+    f = rules.packed_min_cells_per_cu
+    at = lambda S, R, fp32, waves, cells: 0 < f(S, R, fp32, waves) <= cells
+    for S, R, fp32, waves, cells in ((3, 3, 0, 16, 40), (9, 30, 0, 16, 32), (16, 64, 0, 10, 32),
+                                     (9, 100, 0, 13, 48), (8, 150, 0, 10, 128),
+                                     (16, 100, 1, 11, 128), (14, 100, 0, 9, 256), (21, 84, 1, 16, 96)):
+        assert at(S, R, fp32, waves, cells), (S, R, fp32)
+    for S, R, fp32, waves, cells in ((3, 3, 0, 16, 39), (9, 100, 0, 13, 32), (8, 150, 0, 10, 64),
+                                     (16, 100, 0, 9, 128), (9, 200, 0, 8, 256), (9, 300, 1, 5, 256),
+                                     (16, 400, 0, 4, 1024), (21, 84, 0, 13, 1024), (21, 325, 0, 7, 1024),
+                                     (21, 84, 1, 16, 64), (21, 160, 1, 13, 192)):
+        assert not at(S, R, fp32, waves, cells), (S, R, fp32)
