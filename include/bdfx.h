@@ -126,7 +126,8 @@ typedef struct {
                             for bdfx_adjoint(); 0: no recording */
   int32_t waves_per_block; /* 0 = library choice / autotuned value */
   int32_t blocks_per_cu;   /* persistent grid: resident blocks per CU (0 = auto) */
-  int32_t queue_chunk;     /* cells per work-queue pop (0 = 1) */
+  int32_t queue_chunk;     /* cells per work-queue pop (0 = 1), bounded by the library so that
+                              the 32-bit queue counter cannot wrap */
   int32_t waves_per_simd;  /* register budget of the integrator kernel: 0 = the library's
                               choice by the number of cells, 3, 4 or 5 = code built for that
                               many resident waves per SIMD (at most 168 / 128 / 96 VGPRs,
@@ -138,10 +139,11 @@ typedef struct {
   int32_t cells_per_wave;  /* 0 or 1; 2 = each half-wave integrates its own cell
                               (mechanisms of at most 32 species).  With 0 or 1 and
                               waves_per_simd = 0 the library puts two or four isothermal
-                              cells of at most 21 species on a wave, each on its own lanes,
-                              where the cells are many (analytic Jacobian, no lock-step, no
-                              checkpoints); the results are those of one cell per wave,
-                              bit for bit */
+                              cells of at most 21 species (above 16 with lu_precision 32) on
+                              a wave, each on its own lanes, where the cells are many, and
+                              the more the more reactions there are (analytic Jacobian, no
+                              lock-step, no checkpoints, at most 4 waves per block); the
+                              results are those of one cell per wave, bit for bit */
   int32_t jacobian;        /* BDFX_JAC_ANALYTIC (0) or BDFX_JAC_DQ (1): Newton matrix from
                               forward difference quotients, one right-hand side per state
                               entry (Table 1, approaches 3A/3B) */
@@ -390,7 +392,10 @@ typedef struct {
 } bdfx_record_layout;
 int bdfx_get_record_layout(bdfx_ctx ctx, bdfx_record_layout *out);
 
-/* Launch shape of the integrator for the cells of one mechanism. */
+/* Launch shape of the integrator for the cells of one mechanism, as it was set by
+ * the options, bdfx_autotune() or bdfx_set_tuning().  waves_per_simd 0 with
+ * cells_per_wave 1 leaves the register budget, and whether several cells share a
+ * wave, to the library (bdfx_options); what it chose is not reported here. */
 typedef struct {
   int32_t mech;            /* mechanism index (as in d_cell_mech) */
   int32_t waves_per_simd;  /* 0, 3, 4 or 5, as bdfx_options.waves_per_simd */
@@ -416,16 +421,19 @@ typedef struct {
  * {0, 3, 4, 5} x waves_per_block in {1, 2, 4} x queue_chunk in {1, 4} for the
  * queue scheduler) integrating the first min(sample_cells,
  * 16384) cells of that mechanism over [t0, t_out] with HIP events, and keeps
- * the fastest; sample_cells <= 0 means 16384.  The sampled states are saved
- * in the workspace and restored after every trial; their d_status / d_stats
- * entries are overwritten.  out: [n_mech] results in launch order (larger
- * mechanisms first), or NULL.  Synchronises the stream.  The choice holds
- * until the next bdfx_bind(). */
+ * the fastest; sample_cells <= 0 means 16384.  Shapes that run the same code are
+ * timed once.  The library's own choice (waves_per_simd 0) is the one for all
+ * cells of the mechanism; where it would be another for a batch of the sample's
+ * size, the sample cannot judge it and only shapes with it are timed.  The
+ * sampled states are saved in the workspace and restored after every trial;
+ * their d_status / d_stats entries are overwritten.  out: [n_mech] results in
+ * launch order (larger mechanisms first), or NULL.  Synchronises the stream.
+ * The choice holds until the next bdfx_bind(). */
 int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, bdfx_tuning *out);
 /* Apply launch shapes chosen earlier (for example cached results of
  * bdfx_autotune()); entries name their mechanism; the rest are ignored. */
 int bdfx_set_tuning(bdfx_ctx ctx, const bdfx_tuning *tunings, int32_t n);
-/* The launch shape in effect for every mechanism (after bdfx_bind(),
+/* The launch shape of every mechanism (after bdfx_bind(),
  * bdfx_autotune() or bdfx_set_tuning()), in launch order: out[k] for
  * k < min(n, n_mech); sample_cells and ms are 0 unless the shape came from
  * bdfx_autotune() in this binding.  Host-only. */

@@ -416,16 +416,21 @@ class Integrator:
     def autotune(self, t0, t_out, sample_cells=0, cache=None):
         """Pick the launch shape per mechanism with bdfx_autotune().  With
         ``cache`` (a JSON file path, one per machine) results are looked up by
-        compute-unit count, mechanism size, LU precision, scheduler and
-        linear solver, and stored after tuning."""
+        compute-unit count, mechanism size, cells per compute unit, LU
+        precision, scheduler and linear solver, and stored after tuning."""
         import json
 
         # the cache file belongs to one machine; the key tells apart batch
-        # shapes and GPUs of different size
+        # shapes and GPUs of different size.  What is fastest with fewer cells
+        # than waves is not with many (below 8, 32 and 128 cells a compute unit,
+        # and more)
         n_cu = self.torch.cuda.get_device_properties(self.dev).multi_processor_count
+        cells = (np.array([self.N]) if self.cell_mech is None else
+                 np.bincount(self.cell_mech.cpu().numpy(), minlength=len(self.mechs)))
+        size = np.searchsorted([8, 32, 128], cells / n_cu, side="right")
         key = lambda m: (f"CU{n_cu}|S{self.mechs[m]['n_species']}|R{self.mechs[m]['n_reactions']}"
                          f"{'|thermal' if self.mechs[m].get('cv') is not None else ''}"
-                         f"|lu{self.opts.lu_precision}|sched{self.opts.scheduler}"
+                         f"|cells{size[m]}|lu{self.opts.lu_precision}|sched{self.opts.scheduler}"
                          f"{'|dq' if self.opts.jacobian else ''}"
                          f"{f'|gmres{self.opts.gmres_maxl}' if self.opts.gmres_maxl else ''}"
                          f"{f'|lock{self.opts.lockstep}' if self.opts.lockstep else ''}")
@@ -448,7 +453,7 @@ class Integrator:
         return res
 
     def tuning(self):
-        """Launch shape in effect per mechanism (bdfx_get_tuning())."""
+        """Launch shape per mechanism (bdfx_get_tuning())."""
         return bdfx_get_tuning(self.ctx, len(self.mechs))
 
     def outer_loop(self, n_outer, dt, seed, amplitude, t0=0.0, typical_every=0, eta=1e-10):

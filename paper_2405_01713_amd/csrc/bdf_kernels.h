@@ -160,7 +160,7 @@ template <int SA, int SB>
 const void *pair_kernel(bool fp32, int minw, int taba) {
   using F = const void *;
   if (minw >= 5) return nullptr;  // built for the budgets 0, 3 and 4
-  // one register budget per precision: the larger mechanism's (see by_budget)
+  // one register budget per precision: the larger mechanism's (see budget_waves)
   static const F t[2][3] = {
       {F(&k_integrate_pair<SA, SB, double, 2, kTabRxGlobal>), F(&k_integrate_pair<SA, SB, double, 2, kTabLds>),
        F(&k_integrate_pair<SA, SB, double, 2, kTabGlobal>)},
@@ -233,7 +233,7 @@ const void *adjoint_kernel(int kind, bool abc) {
 // lock-step kernels: one register budget, one cell per wave, tables in LDS
 template <int S>
 const void *lock_kernel(bool fp32, bool abc) {
-  // (above 32 species as many waves per SIMD as in by_budget; below, the block of
+  // (above 32 species as many waves per SIMD as in budget_waves; below, the block of
   // up to 16 waves bounds the registers)
   constexpr int W8 = S > 32 ? 2 : 1, W4 = S > 32 ? 3 : 1;
   if (abc)
@@ -243,27 +243,38 @@ const void *lock_kernel(bool fp32, bool abc) {
               : (const void *)&k_integrate<S, double, W8, kTabLds, 1, false, false, kLinAnalytic, true>;
 }
 
+// Waves per SIMD that the kernel of register budget w (0; 1, 2, 3 for 3, 4, 5) is
+// built for, G cells per wave.
+// The tiled elimination keeps the whole matrix in registers, so above 32
+// species a budget for more waves than the LDS lets reside (the inverse: two
+// waves per SIMD in FP64, three in FP32) only spills it: 53 species FP64 at
+// the 3-wave budget took 44 ms on 4,096 cells against 25.
+// Budget 0, the compiler's choice (1), is bounded where the elimination would take
+// more registers than leave the waves the LDS has room for.  Not with two cells
+// per wave, whose row form spills under it, ms bounded / not: FP64, 30 species
+// 55.9 / 50.1 on 8,192 cells, 184 / 166 on 32,768, 21 species 11.0 / 10.1 on
+// 2,048, 67.2 / 68.3 on 32,768; FP32, 30 species 31.6 / 30.5 on 8,192.
+__host__ __device__ constexpr int budget_waves(int S, int lt_bytes, int G, int lin, int w) {
+  if (S > 32 && lin != kLinGmres) {
+    const int cap = lt_bytes == 8 ? 2 : 3;
+    return w == 0 || w + 2 > cap ? cap : w + 2;
+  }
+  return w > 0 ? w + 2 : G == 1 && S > 16 && lin != kLinGmres ? 3 : 1;
+}
+// index of a budget given as waves_per_simd (0, 3, 4 or 5)
+__host__ __device__ constexpr int budget_index(int waves_per_simd) {
+  return waves_per_simd >= 5 ? 3 : waves_per_simd >= 4 ? 2 : waves_per_simd >= 3 ? 1 : 0;
+}
+
 // the register budgets of one kernel configuration
 template <int S, typename LT, int TAB, int G, bool ABC, bool TH = false, int LIN = kLinAnalytic>
 const void *by_budget(int w) {
   using F = const void *;
-  // The tiled elimination keeps the whole matrix in registers, so above 32
-  // species a budget for more waves than the LDS lets reside (the inverse: two
-  // waves per SIMD in FP64, three in FP32) only spills it: 53 species FP64 at
-  // the 3-wave budget took 44 ms on 4,096 cells against 25.
-  constexpr bool kBig = S > 32 && LIN != kLinGmres;
-  constexpr int CAP = kBig ? (sizeof(LT) == 8 ? 2 : 3) : 5;
-  // budget 0, the compiler's choice: bounded where the elimination would take
-  // more registers than leave the waves the LDS has room for.  Not with two cells
-  // per wave, whose row form spills under it, ms bounded / not: FP64, 30 species
-  // 55.9 / 50.1 on 8,192 cells, 184 / 166 on 32,768, 21 species 11.0 / 10.1 on
-  // 2,048, 67.2 / 68.3 on 32,768; FP32, 30 species 31.6 / 30.5 on 8,192.
-  constexpr int W0 = kBig ? CAP : G == 1 && S > 16 && LIN != kLinGmres ? 3 : 1;
-  constexpr int W3 = CAP < 3 ? CAP : 3, W4 = CAP < 4 ? CAP : 4, W5 = CAP;
-  static const F t[4] = {F(&k_integrate<S, LT, W0, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, W3, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, W4, TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, W5, TAB, G, ABC, TH, LIN>)};
+  constexpr int B = sizeof(LT);
+  static const F t[4] = {F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 0), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 1), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 2), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 3), TAB, G, ABC, TH, LIN>)};
   return t[w];
 }
 
@@ -318,7 +329,7 @@ const void *integrate_kernel_abc(bool fp32, int w, int tab, int cells_per_wave) 
 template <int S>
 const void *integrate_kernel(bool fp32, int minw, int tab, int cells_per_wave, bool abc,
                              bool thermal, int lin, bool lock = false) {
-  const int w = minw >= 5 ? 3 : minw >= 4 ? 2 : minw >= 3 ? 1 : 0;
+  const int w = budget_index(minw);
   if (lock) {
     if (tab != kTabLds || cells_per_wave != 1 || thermal || lin != kLinAnalytic) return nullptr;
     return lock_kernel<S>(fp32, abc);

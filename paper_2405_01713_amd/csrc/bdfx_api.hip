@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -139,6 +140,7 @@ struct bdfx_mech_s {
 struct Bin {
   int mech;
   int64_t offset, count;
+  int64_t kernel_cells = 0;  // cells by which the kernel is chosen: the bin's, also for a sample of it
   // launch of the integrator for this bin, fixed at bind time so that
   // bdfx_integrate() only enqueues kernels (it may be captured in a graph)
   const SizeEntry *se = nullptr;
@@ -627,7 +629,7 @@ static int configure_packed(bdfx_ctx ctx, Bin &b) {
   int occ = 0;
   HIPCHK(ctx, b.se->occupancy_packed(fp32, m->abc, bdfx::kWave * waves, lds, &occ));
   const int64_t least = bdfx::packed_min_cells_per_cu(b.se->S, m->R, fp32, occ * waves);
-  if (occ < 1 || least == 0 || b.count < least * ctx->n_cu) return BDFX_OK;
+  if (occ < 1 || least == 0 || b.kernel_cells < least * ctx->n_cu) return BDFX_OK;
   b.packed = cells;
   b.lds_doubles = d;
   b.tab = bdfx::kTabLds;
@@ -692,13 +694,13 @@ static int budget_of(bdfx_ctx ctx, const Bin &b, int waves, size_t lds_bytes, in
   const int64_t simds = 4 * static_cast<int64_t>(ctx->n_cu);
   // (two waves a SIMD fit whatever the compiler took)
   if (b.waves_per_simd != 0 || most == 0 || b.cells_per_wave != 1 || ctx->opt.lockstep > 0 ||
-      lds_bytes > 65536 || b.count <= 2 * simds)
+      lds_bytes > 65536 || b.kernel_cells <= 2 * simds)
     return BDFX_OK;
   int occ0 = 0, occ = 0;
   HIPCHK(ctx, b.se->occupancy(fp32, 0, bdfx::kTabLds, 1, kernel_flags(ctx, m), bdfx::kWave * waves,
                               lds_bytes, &occ0));
-  if (b.count <= static_cast<int64_t>(occ0) * waves * ctx->n_cu) return BDFX_OK;
-  const int w = static_cast<int>(std::min<int64_t>((b.count + simds - 1) / simds, most));
+  if (b.kernel_cells <= static_cast<int64_t>(occ0) * waves * ctx->n_cu) return BDFX_OK;
+  const int w = static_cast<int>(std::min<int64_t>((b.kernel_cells + simds - 1) / simds, most));
   HIPCHK(ctx, b.se->occupancy(fp32, w, bdfx::kTabLds, 1, kernel_flags(ctx, m), bdfx::kWave * waves,
                               lds_bytes, &occ));
   if (occ > occ0) *budget = w;
@@ -868,6 +870,7 @@ static hipError_t launch_pair(bdfx_ctx ctx, const Bin &a, const Bin &b, bdfx::Pa
 // Kernel, LDS size and grid of every bin (called by bdfx_bind).
 static int configure_bins(bdfx_ctx ctx) {
   for (Bin &b : ctx->bins) {
+    b.kernel_cells = b.count;
     if (!b.tuned) {
       b.waves_per_simd = ctx->opt.waves_per_simd;
       b.waves_per_block = ctx->opt.waves_per_block > 0 ? ctx->opt.waves_per_block : 1;
@@ -1091,17 +1094,42 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
     float best = 0.0f;
     bool have = false;
     Bin pick = b;
+    // Where the library's own kernel for the bin (packing, register budget) is not
+    // the one it would take for as few cells as the sample, the sample says
+    // nothing about the others: they have waves to spare on it that the bin does
+    // not leave them.  Then only the library's kernel is timed.
+    bool own_only = false;
+    if (trial.count < b.count) {
+      Bin lib = b, few = b;
+      for (Bin *k : {&lib, &few}) {
+        k->cells_per_wave = k->waves_per_block = 1;
+        k->waves_per_simd = 0;
+      }
+      few.kernel_cells = trial.count;
+      own_only = configure_bin(ctx, lib) == BDFX_OK && configure_bin(ctx, few) == BDFX_OK &&
+                 (lib.packed != few.packed || (lib.packed == 1 && lib.budget != few.budget));
+    }
+    // kernels timed with a block shape and chunk: several budgets may be one kernel
+    std::vector<std::array<int, 4>> timed;
     for (int cpw : cpw_c)
     for (int wps : wps_c)
       for (int wpb : wpb_c)
         for (int chunk : chunk_c) {
           if (!queue && chunk != 1) continue;
           if (cpw == 2 && !two_cells_per_wave_ok(ctx, m, b.se->S)) continue;
+          if (own_only && (cpw != 1 || wps != 0)) continue;
           trial.cells_per_wave = cpw;
           trial.waves_per_simd = wps;
           trial.waves_per_block = wpb;
           trial.queue_chunk = chunk;
           if (configure_bin(ctx, trial) != BDFX_OK) continue;  // e.g. LDS too large
+          if (trial.packed == 1) {
+            const int w = bdfx::budget_waves(b.se->S, ctx->opt.lu_precision == 32 ? 4 : 8, cpw, lin_of(ctx),
+                                             bdfx::budget_index(trial.budget));
+            const std::array<int, 4> shape = {cpw, w, wpb, chunk};
+            if (std::find(timed.begin(), timed.end(), shape) != timed.end()) continue;
+            timed.push_back(shape);
+          }
           float total = 0.0f;
           hipError_t e = hipSuccess;
           for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {  // rep 0 warms up
