@@ -943,6 +943,7 @@ __device__ __forceinline__ void write_identity(LT *M, const Grp<G> &W, int c0) {
 #pragma unroll
   for (int e = 0; e + L <= N; e += L) M[e + W.lane] = static_cast<LT>(0);
   if (N % L && W.lane < N % L) M[N / L * L + W.lane] = static_cast<LT>(0);
+  wave_lds_sync();  // (another lane zeroed the lane's diagonal entry)
   if (W.lane >= c0 && W.lane < c0 + NC) M[(W.lane - c0) * S + W.lane] = static_cast<LT>(1);
 }
 
