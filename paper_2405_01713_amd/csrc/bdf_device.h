@@ -1493,10 +1493,11 @@ __device__ __forceinline__ int panel_step(LT (&a)[4], LT &q, int row, int k, int
     p = static_cast<int>(__builtin_ctzll(__ballot(key == kmax)));
     zero_pivot = kmax <= 1u;
   } else {
-    // high words first (one more than the magnitude's, 0 on used rows), then
-    // the low words of the rows that tie on them
+    // high words first (one more than the magnitude's, and 1 on used rows, with
+    // which a zero pivot ties even where one unused row is left), then the low
+    // words of the unused rows that tie on them
     const uint64_t bits = __builtin_bit_cast(uint64_t, a[E]);
-    const uint32_t hi = piv < 0 ? (static_cast<uint32_t>(bits >> 32) & 0x7fffffffu) + 1u : 0u;
+    const uint32_t hi = piv < 0 ? (static_cast<uint32_t>(bits >> 32) & 0x7fffffffu) + 1u : 1u;
     // the search's rounds and the refinement of the reciprocal (rcp()), turn
     // by turn: a wave issues in order, and either chain alone waits
     const LT x = a[E];
@@ -1523,12 +1524,11 @@ __device__ __forceinline__ int panel_step(LT (&a)[4], LT &q, int row, int k, int
     const uint64_t tie = __ballot(hi == hmax) & kLanes;
     p = static_cast<int>(__builtin_ctzll(tie | (1ull << 63)));
     zero_pivot = false;
-    // (a lone maximum of 1 is the last unused row, or a denormal pivot: the low
-    // words tell a zero)
-    if (__builtin_expect(__builtin_popcountll(tie) != 1 || hmax == 1u, 0)) {
+    if (__builtin_expect(__builtin_popcountll(tie) != 1, 0)) {
       const uint32_t lo = static_cast<uint32_t>(bits);
-      const uint32_t lmax = W.template max_u32<(S + 15) / 16>(hi == hmax ? lo : 0u);
-      p = static_cast<int>(__builtin_ctzll(__ballot(hi == hmax && lo == lmax) | (1ull << 63)));
+      const bool in = piv < 0 && hi == hmax;
+      const uint32_t lmax = W.template max_u32<(S + 15) / 16>(in ? lo : 0u);
+      p = static_cast<int>(__builtin_ctzll(__ballot(in && lo == lmax) | (1ull << 63)));
       zero_pivot = hmax == 1u && lmax == 0u;
     }
   }
