@@ -381,11 +381,12 @@ struct Grp {
 // The same lane group with a lane index the optimizer cannot trace: addresses
 // formed from it are computed where they are used instead of being hoisted out
 // of the integration's loops and kept in registers (at 53 species that held
-// some 30 VGPRs through the elimination, as much as it then spilled).
-template <int G>
+// some 30 VGPRs through the elimination, as much as it then spilled).  LOC false:
+// the lane group as it is.
+template <bool LOC = true, int G>
 __device__ __forceinline__ Grp<G> local_lane(const Grp<G> &W) {
   Grp<G> V = W;
-  asm volatile("" : "+v"(V.lane));
+  if constexpr (LOC) asm volatile("" : "+v"(V.lane));
   return V;
 }
 
@@ -472,10 +473,10 @@ __device__ __forceinline__ void bdf_coeffs(int q, const double (&xi)[kQmax + 2],
 // coefficient l_j, which takes the factors (1 + x/xi_i) in turn from its
 // neighbour's.  The operations of bdf_coeffs on each entry.  Every lane gets
 // l_1 and Cerr.  DIV: xi_i by a division instead of the product with 1 / h.
-template <bool DIV = false, int G>
+template <bool DIV = false, bool LOC = true, int G>
 __device__ __forceinline__ void step_coeffs(int q, double h, double *C, const double *hist, int kxi,
                                             int kl, const Grp<G> &W, double &l1, double &Cerr) {
-  const int i = local_lane(W).lane;
+  const int i = local_lane<LOC>(W).lane;
   double sum = h;
 #pragma unroll
   for (int k = 0; k <= kQmax - 1; ++k) {
@@ -793,13 +794,13 @@ __device__ __forceinline__ void thermal_rates(const MechDev &m, const Lds &L, in
 // state is exchanged.  With the tables in global memory (NP = 6, all of a
 // 325-reaction mechanism) a right-hand side then waits for memory once instead
 // of once per two passes.
-template <bool ABC, bool TH = false, int NP = 2, int G>
+template <bool ABC, bool TH = false, int NP = 2, bool LOC = true, int G>
 __device__ __forceinline__ double rhs(const MechDev &m, const Lds &L, const Grp<G> &W, double yi,
                                       double Fi, int ns = 0) {
   const int R = m.R;
   int2 w[NP];
   double k[NP][2];
-  const int lane = local_lane(W).lane;
+  const int lane = local_lane<LOC>(W).lane;
   auto load = [&](int r0) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -1187,7 +1188,7 @@ __device__ __forceinline__ double wrms2(const Grp<G> &W, double v, double w, dou
 // min_inc / w_j), column j = (f(y + inc_j e_j) - f0) / inc_j.  Columns are
 // written to the LDS matrix area (padding entries keep the identity), then
 // each lane reads its row.  Costs n + 1 right-hand sides.
-template <int S, typename LT, bool ABC, bool TH, int G>
+template <int S, typename LT, bool ABC, bool TH, bool LOC, int G>
 __device__ __forceinline__ void dq_matrix(Mat<S, LT, G> &a, const MechDev &m, const Lds &L, const Grp<G> &W,
                                           double y, double Fi, double gamma, double h, double ewt,
                                           int ns, int n, double inv_n) {
@@ -1203,7 +1204,7 @@ __device__ __forceinline__ void dq_matrix(Mat<S, LT, G> &a, const MechDev &m, co
       inc = W.uni(sy > sm ? sy : sm);
       if (W.lane == j) yp = yj + inc;
     }
-    const double f = rhs<ABC, TH>(m, L, W, yp, Fi, ns);
+    const double f = rhs<ABC, TH, 2, LOC>(m, L, W, yp, Fi, ns);
     if (j < 0) {
       f0 = f;
       const double fnorm = W.uni(sqrt(wrms2<S>(W, f0, ewt, inv_n)));
@@ -1365,7 +1366,7 @@ __device__ __forceinline__ void gj_block(LT (&a)[S], const Grp<G> &W, int k0, in
 // that a solve is one lane-parallel matrix-vector product.  Returns 0, or k+1
 // for the first column k without a nonzero pivot (the elimination then runs on
 // garbage).
-template <int S, typename LT, int T = 0, int G>
+template <int S, typename LT, int T = 0, bool LOC = true, int G>
 __device__ __forceinline__ int invert(RowMat<S, LT> &m, const Grp<G> &W, const Lds &L, int n,
                                       InvTail<T, LT> *tail = nullptr) {
   static_assert(T == 0 && S <= 32, "larger matrices take the tiled form");
@@ -1647,11 +1648,11 @@ __device__ __forceinline__ void mx_tile_row(TileMat<S, LT> &m, const Grp<1> &W, 
 // 53 species FP64: 2,040 -> 1,287 instructions per cell and step, 43.2 -> 37.8 ms
 // for 8,192 cells.  Up to 16 species there is one tile, mostly padding, and a
 // row holds few entries: rows stay.
-template <int S, typename LT, int T = 0>
+template <int S, typename LT, int T = 0, bool LOC = true>
 __device__ __forceinline__ int invert(TileMat<S, LT> &m, const Grp<1> &W, const Lds &L, int n,
                                       InvTail<T, LT> *tail = nullptr) {
   constexpr int NT = TileMat<S, LT>::NT;
-  const Grp<1> V = local_lane(W);
+  const Grp<1> V = local_lane<LOC>(W);
   const int li = V.lane, j = li & 15, g = li >> 4;
   const int row = NT == 2 ? li & 31 : li;
   int piv = row < n ? -1 : row;
@@ -1744,10 +1745,10 @@ __device__ __forceinline__ int invert(TileMat<S, LT> &m, const Grp<1> &W, const 
 // SPLIT: three partial sums (FP32 inverse of isothermal kernels, see below).
 // T > 0 (slot order with a register tail, invert()): the sum runs over the
 // slots k, b_{p_k} gathered to lane k first.
-template <int S, typename LT, bool SPLIT, int T = 0, int G>
+template <int S, typename LT, bool SPLIT, int T = 0, bool LOC = true, int G>
 __device__ __forceinline__ double inv_solve(const Lds &L, const Grp<G> &W, double b,
                                             const InvTail<T, LT> *tail = nullptr) {
-  const Grp<G> V = local_lane(W);
+  const Grp<G> V = local_lane<LOC>(W);
   const LT *inv = reinterpret_cast<const LT *>(L.fac);
   LT *bb = reinterpret_cast<LT *>(L.yb);
   if constexpr (T > 0) {
@@ -1878,7 +1879,7 @@ struct BatchRed {
 // inlined once.  Returns 0 when converged, 1 when the residual was reduced
 // but not to delta, 2 otherwise; x receives the lane's solution entry and
 // nli the iterations (one right-hand side each).
-template <int S, bool ABC, bool TH, int G>
+template <int S, bool ABC, bool TH, bool LOC, int G>
 __device__ int gmres(const MechDev &m, const Lds &L, const Grp<G> &W, double y, double fy,
                      double Fi, double ewt, double gamma, double b, int maxl, double delta,
                      int ns, int n, double inv_n, double &x, int &nli) {
@@ -1908,7 +1909,7 @@ __device__ int gmres(const MechDev &m, const Lds &L, const Grp<G> &W, double y, 
     // and J v = (f(y + sigma v) - f(y)) ||v||
     const double vl = own ? kb[K.V + l * S + li] : 0.0;
     const double v = vl * rw;
-    const double fp = rhs<ABC, TH>(m, L, W, y + sigma * v, Fi, ns);
+    const double fp = rhs<ABC, TH, 2, LOC>(m, L, W, y + sigma * v, Fi, ns);
     nli++;
     double w = own ? ewt * (v - gamma * ((fp - fy) * vn)) : 0.0;
     // modified Gram-Schmidt: column l of the Hessenberg matrix
@@ -1967,16 +1968,17 @@ __device__ int gmres(const MechDev &m, const Lds &L, const Grp<G> &W, double y, 
 }
 
 // RES: a resumed integration (Resume); its Newton matrix is the analytic one
-// in FP64, one cell per wave.
+// in FP64, one cell per wave.  HOIST: the lane's addresses are the compiler's to
+// keep (hoist_lane).
 template <int S, typename LT, int TAB, int G, bool ABC, bool TH, int LIN, bool LOCK = false,
-          bool RES = false>
+          bool RES = false, bool HOIST = false>
 __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, const Grp<G> &W,
                                                double *lds, double *kk_slot,
                                                BatchRed<LOCK> br = BatchRed<LOCK>{},
                                                int batch_cells = 1, const Resume *rs = nullptr) {
   static_assert(!RES || (G == 1 && !LOCK && !TH && LIN == kLinAnalytic && sizeof(LT) == 8),
                 "resumed integrations: FP64 direct solver, analytic Jacobian, one cell per wave");
-  constexpr bool KRY = LIN == kLinGmres;
+  constexpr bool KRY = LIN == kLinGmres, LOC = !HOIST;
   constexpr int NP = TAB == kTabGlobal ? 6 : 2;  // reaction passes loaded ahead
   const MechDev &m = P.mech;
   const int R = m.R;
@@ -2070,7 +2072,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       const double zs = own ? ck[Ckpt::vec(Ckpt::kVecSetup, S) + W.lane] : 0.0;
       Mat<S, LT, G> a;
       newton_matrix<S, LT, ABC, TL>(a, m, L, W, zs, uni(ck[Ckpt::kGammaBar]), false);
-      invert<S, LT, TL>(a, W, L, n, &itail);
+      invert<S, LT, TL, LOC>(a, W, L, n, &itail);
     }
   } else {
     const double yin = own ? P.y[cell * P.ldy + W.lane] : 0.0;
@@ -2081,7 +2083,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
     }
     if (status == kSuccess) {
       z[0] = yin;
-      f = rhs<ABC, TH, NP>(m, L, W, yin, Fi, ns);
+      f = rhs<ABC, TH, NP, LOC>(m, L, W, yin, Fi, ns);
       nfe = 1;
       if (br.any(W.any(own && !isfinite(f)))) {
         status = kNonfinite;
@@ -2103,7 +2105,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
         double hg = sqrt(hlb * hub), hnew = hg;
         bool at_ub = false;
         for (int it = 0; it < 4; ++it) {
-          const double ft = rhs<ABC, TH, NP>(m, L, W, yin + hg * f, Fi, ns);
+          const double ft = rhs<ABC, TH, NP, LOC>(m, L, W, yin + hg * f, Fi, ns);
           nfe++;
           const double ydd = (ft - f) / hg;
           const double yddnrm = sqrt(norm2(ydd, ewt));
@@ -2199,7 +2201,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       }
       nd_predict(z);
       double l1;
-      step_coeffs(q, h, C, C + Ctl::kHist, Ctl::kXi, Ctl::kL, W, l1, Cerr);
+      step_coeffs<false, LOC>(q, h, C, C + Ctl::kHist, Ctl::kXi, Ctl::kL, W, l1, Cerr);
       C[Ctl::kTn] = landing ? tout : plain_sum(t, h);
       const double rl1 = W.uni(rcp(l1));
       const double gamma = W.uni(h * rl1);
@@ -2217,14 +2219,14 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
           {
             Mat<S, LT, G> a;
             if constexpr (LIN == kLinDq) {
-              dq_matrix<S, LT, ABC, TH>(a, m, L, W, z[0], Fi, gamma, h, ewt, ns, n, inv_n);
+              dq_matrix<S, LT, ABC, TH, LOC>(a, m, L, W, z[0], Fi, gamma, h, ewt, ns, n, inv_n);
               nfe += n + 1;
             } else if constexpr (TH) {
               newton_matrix_thermal<S, LT>(a, m, L, W, z[0], Fi, gamma, ns);
             } else {
               newton_matrix<S, LT, ABC, TL>(a, m, L, W, z[0], gamma, false);
             }
-            info = invert<S, LT, TL>(a, W, L, n, &itail);
+            info = invert<S, LT, TL, LOC>(a, W, L, n, &itail);
           }
           if (!RES && P.ckpt && own) P.ckpt_setup[cell * P.ckpt_vs + W.lane] = z[0];
           nsetups++;
@@ -2263,7 +2265,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
       const double tol2 = 0.01 * W.uni(rcp(Cerr * Cerr));
       e = 0.0;
       for (int mit = 0; mit < 3; ++mit) {
-        f = rhs<ABC, TH, NP>(m, L, W, z[0] + e, Fi, ns);
+        f = rhs<ABC, TH, NP, LOC>(m, L, W, z[0] + e, Fi, ns);
         nfe++;
         nni++;
         const double Gi = e - gamma * f + z[1] * rl1;
@@ -2272,14 +2274,14 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
           // inexact Newton: J at the current iterate; a reduced but
           // unconverged residual is accepted on the first iteration only
           int nl = 0;
-          const int lret = gmres<S, ABC, TH>(m, L, W, z[0] + e, f, Fi, ewt, gamma, -Gi,
+          const int lret = gmres<S, ABC, TH, LOC>(m, L, W, z[0] + e, f, Fi, ewt, gamma, -Gi,
                                              P.gmres_maxl, ltol, ns, n, inv_n, delta, nl);
           nli += nl;
           nfe += nl;
           if (lret != 0) ncfl++;
           if (lret == 2 || (lret == 1 && mit > 0)) break;
         } else {
-          delta = inv_solve<S, LT, sizeof(LT) == 4 && !TH, TL>(L, W, -Gi, &itail);
+          delta = inv_solve<S, LT, sizeof(LT) == 4 && !TH, TL, LOC>(L, W, -Gi, &itail);
           if (cfac != 1.0) delta *= cfac;
         }
         e = plain_sum(e, delta);
@@ -2328,7 +2330,7 @@ __device__ __forceinline__ void integrate_cell(const Params &P, int64_t cell, co
         // restart at order 1 from the last accepted y
         const double hnew = W.uni(0.1 * h);
         q = 1;
-        const double f0 = rhs<ABC, TH, NP>(m, L, W, z[0], Fi, ns);
+        const double f0 = rhs<ABC, TH, NP, LOC>(m, L, W, z[0], Fi, ns);
         nfe++;
 #pragma unroll
         for (int j = 2; j <= kQmax; ++j) z[j] = 0.0;

@@ -11,6 +11,18 @@
 
 namespace bdfx {
 
+// Whether a kernel leaves its lane's addresses to the compiler (local_lane): those
+// for few cells whose steps are many right-hand sides or re-evaluate the rate
+// constants, where registers are free (MINW 1) and forming the addresses anew is
+// what waits.  ms, formed anew / left, 1,024 cells: difference quotients 9 species
+// FP64 3.10 / 2.91, 18 FP32 4.38 / 4.10, non-isothermal 9 species FP64 3.41 / 3.31,
+// 30 species FP64 7.38 / 7.17.  With the analytic Jacobian it is the other way: 21
+// species FP64 3.79 / 4.08, 30 species 6.35 / 6.97; above 32 species too (53
+// species FP64 11.1 / 13.2) or even.
+constexpr bool hoist_lane(int S, int MINW, bool TH, int LIN) {
+  return (TH || LIN != kLinAnalytic) && S <= 32 && MINW == 1;
+}
+
 // Threads of the largest lock-step block.  Above 32 species the matrix tiles
 // alone take up to 128 registers, all that blocks of 16 waves would leave a
 // lane, while the LDS of a block (64 KiB) holds few waves: 2 at 53 species in
@@ -98,7 +110,8 @@ __global__ void __launch_bounds__(LOCK ? lock_threads(S, sizeof(LT)) : 256, MINW
     if (next >= P.n_list) break;
     const int64_t cell = P.list ? P.list[next] : next;
     ++next;
-    integrate_cell<S, LT, TAB, G, ABC, TH, LIN>(P, cell, W, lds, kk_slot);
+    integrate_cell<S, LT, TAB, G, ABC, TH, LIN, false, false, hoist_lane(S, MINW, TH, LIN)>(P, cell, W, lds,
+                                                                                            kk_slot);
   }
 }
 
@@ -249,17 +262,20 @@ const void *lock_kernel(bool fp32, bool abc) {
 // species a budget for more waves than the LDS lets reside (the inverse: two
 // waves per SIMD in FP64, three in FP32) only spills it: 53 species FP64 at
 // the 3-wave budget took 44 ms on 4,096 cells against 25.
-// Budget 0, the compiler's choice (1), is bounded where the elimination would take
-// more registers than leave the waves the LDS has room for.  Not with two cells
-// per wave, whose row form spills under it, ms bounded / not: FP64, 30 species
-// 55.9 / 50.1 on 8,192 cells, 184 / 166 on 32,768, 21 species 11.0 / 10.1 on
-// 2,048, 67.2 / 68.3 on 32,768; FP32, 30 species 31.6 / 30.5 on 8,192.
-__host__ __device__ constexpr int budget_waves(int S, int lt_bytes, int G, int lin, int w) {
+// Budget 0 is the compiler's choice (1), but for three waves above 16 species with
+// the isothermal analytic Jacobian, which is 1 % faster there.  Not with the
+// temperature or difference quotients, whose steps need the registers, ms bounded /
+// not, 1,024 cells FP64: non-isothermal 20 species 3.64 / 3.22, 30 species 7.18 /
+// 6.46; difference quotients 18 species 4.14 / 3.94, 30 species 9.19 / 8.66.  Nor
+// with two cells per wave, whose row form spills under it: 30 species FP64 55.9 / 50.1
+// on 8,192 cells, 184 / 166 on 32,768, 21 species 11.0 / 10.1 on 2,048, 67.2 / 68.3
+// on 32,768.
+__host__ __device__ constexpr int budget_waves(int S, int lt_bytes, int G, bool thermal, int lin, int w) {
   if (S > 32 && lin != kLinGmres) {
     const int cap = lt_bytes == 8 ? 2 : 3;
     return w == 0 || w + 2 > cap ? cap : w + 2;
   }
-  return w > 0 ? w + 2 : G == 1 && S > 16 && lin != kLinGmres ? 3 : 1;
+  return w > 0 ? w + 2 : G == 1 && S > 16 && !thermal && lin == kLinAnalytic ? 3 : 1;
 }
 // index of a budget given as waves_per_simd (0, 3, 4 or 5)
 __host__ __device__ constexpr int budget_index(int waves_per_simd) {
@@ -271,10 +287,10 @@ template <int S, typename LT, int TAB, int G, bool ABC, bool TH = false, int LIN
 const void *by_budget(int w) {
   using F = const void *;
   constexpr int B = sizeof(LT);
-  static const F t[4] = {F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 0), TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 1), TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 2), TAB, G, ABC, TH, LIN>),
-                         F(&k_integrate<S, LT, budget_waves(S, B, G, LIN, 3), TAB, G, ABC, TH, LIN>)};
+  static const F t[4] = {F(&k_integrate<S, LT, budget_waves(S, B, G, TH, LIN, 0), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, TH, LIN, 1), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, TH, LIN, 2), TAB, G, ABC, TH, LIN>),
+                         F(&k_integrate<S, LT, budget_waves(S, B, G, TH, LIN, 3), TAB, G, ABC, TH, LIN>)};
   return t[w];
 }
 

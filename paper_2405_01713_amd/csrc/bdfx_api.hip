@@ -668,16 +668,16 @@ static hipError_t launch_bin(bdfx_ctx ctx, const Bin &b, bdfx::Params P) {
 //   30 species, 4 waves        FP64 34.1 -> 33.3   FP32 35.5 -> 33.0  (5: 34.0, 35.0)
 //   30 species, difference quotients, 4 waves      FP32 46.6 -> 44.5
 //   21 species non-isothermal (the 32-entry kernel), 4 waves  FP32 33.5 -> 30.4
-// It stays for FP64 in the 32-entry kernel with the temperature or difference
-// quotients (33.4 -> 33.9, 52.3 -> 53.3) and for 21 species with FP32
-// difference quotients (9.8 -> 10.0 at 4,096 cells), where the smaller budgets
-// spill, and above 32 species, where the LDS or the matrix in registers bounds
-// the waves.
+// Three waves for FP64 in the 32-entry kernel with the temperature or difference
+// quotients (4 waves 33.4 -> 33.9, 52.3 -> 53.3) and four for 21 species with FP32
+// difference quotients (5 waves 9.8 -> 10.0 at 4,096 cells), where the smaller
+// budgets spill.  The compiler's choice stays above 32 species, where the LDS or
+// the matrix in registers bounds the waves.
 static int most_waves(int S, bool fp32, bool thermal, int lin) {
   if (S > 32) return 0;
   const bool dq = lin == bdfx::kLinDq;
-  if (S > 21) return !fp32 && (thermal || dq) ? 0 : 4;
-  return dq && fp32 && S > 16 ? 0 : 5;
+  if (S > 21) return !fp32 && (thermal || dq) ? 3 : 4;
+  return dq && fp32 && S > 16 ? 4 : 5;
 }
 
 // Register budget of a one-cell-per-wave launch.  With the registers the
@@ -1124,7 +1124,8 @@ int bdfx_autotune(bdfx_ctx ctx, double t0, double t_out, int64_t sample_cells, b
           trial.queue_chunk = chunk;
           if (configure_bin(ctx, trial) != BDFX_OK) continue;  // e.g. LDS too large
           if (trial.packed == 1) {
-            const int w = bdfx::budget_waves(b.se->S, ctx->opt.lu_precision == 32 ? 4 : 8, cpw, lin_of(ctx),
+            const int w = bdfx::budget_waves(b.se->S, ctx->opt.lu_precision == 32 ? 4 : 8, cpw,
+                                             m->thermal, lin_of(ctx),
                                              bdfx::budget_index(trial.budget));
             const std::array<int, 4> shape = {cpw, w, wpb, chunk};
             if (std::find(timed.begin(), timed.end(), shape) != timed.end()) continue;
