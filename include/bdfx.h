@@ -98,8 +98,8 @@ typedef struct {
 
 /* Scheduler for bdfx_options.scheduler */
 #define BDFX_SCHED_STATIC 0 /* one lane group per cell, grid covers every cell (several cells
-                               per wave, see cells_per_wave, pop them from the work queue
-                               under every scheduler) */
+                               per wave, see cells_per_wave, pop them one by one from the
+                               work queue; queue_chunk and blocks_per_cu do not apply) */
 #define BDFX_SCHED_QUEUE 1  /* persistent waves pop cells from an atomic work queue */
 #define BDFX_SCHED_FUSED 2  /* as BDFX_SCHED_QUEUE, and a batch of two mechanisms runs in
                                one launch: each block holds waves for both, the larger
@@ -108,10 +108,10 @@ typedef struct {
                                cells, Sec. 2 and Sec. 4.1.1).  Applies to isothermal
                                A + B <=> C mechanisms on the direct solver with the analytic
                                Jacobian whose padded sizes have a compiled pair (53 with 9);
-                               otherwise the bins are launched one after the other.  One
-                               cell per wave.  bdfx_autotune() also times the one launch
-                               against the per-mechanism launches on its samples and keeps
-                               the faster (bdfx_tuning.fused).  Results equal the
+                               otherwise the bins are launched one after the other.  The
+                               one launch holds one cell per wave.  bdfx_autotune() also
+                               times it against the per-mechanism launches on its samples
+                               and keeps the faster (bdfx_tuning.fused).  Results equal the
                                BDFX_SCHED_QUEUE ones bit for bit. */
 
 typedef struct {

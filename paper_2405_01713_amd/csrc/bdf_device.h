@@ -959,7 +959,7 @@ struct MatOf<S, LT, true> {
 template <int S, typename LT, int G>
 using Mat = typename MatOf<S, LT, (G == 1 && S > 16)>::type;
 
-// Row li of M = I - gamma J (or of M^T when `transposed`) at the state y held
+// M = I - gamma J (or M^T when `transposed`) in registers (Mat), at the state y held
 // by the lanes (lane i passes y_i).  M is assembled in LDS, in the area that
 // afterwards holds the inverse, column-major ((i, c) at c*S + i): starting
 // from the identity, lane r mod 64 takes reaction r, forms d q_r / d y_c for
@@ -967,7 +967,7 @@ using Mat = typename MatOf<S, LT, (G == 1 && S > 16)>::type;
 // that side; the reverse constant is stored negated) and adds
 // -gamma nu_ir d q_r / d y_c to M(i, c) for every occupied slot i of the
 // reaction (reactant slots count -1, product slots +1) with LDS atomics.
-// Each lane then reads its row (its column for M^T).  Terms are rounded to LT
+// The lanes then read their entries of it.  Terms are rounded to LT
 // before they are summed.  T > 0 (an inverse with T slots in registers,
 // whose LDS area holds S - T columns): two passes over the reactions, columns
 // 0 .. S-T-1 and then the last T, each entry with the same terms in the same
@@ -1181,13 +1181,13 @@ __device__ __forceinline__ double wrms2(const Grp<G> &W, double v, double w, dou
   return W.uni(W.template sum<(S + 15) / 16>(t * t) * inv_n);
 }
 
-// Row li of M = I - gamma J with J by forward difference quotients, one
+// M = I - gamma J in registers with J by forward difference quotients, one
 // right-hand side per state entry (Table 1, approaches 3A/3B; increments of
 // the dense difference-quotient scheme documented for CVODE): f0 = f(y),
 // min_inc = 1000 |h| u n ||f0|| (1 if ||f0|| = 0), inc_j = max(sqrt(u) |y_j|,
 // min_inc / w_j), column j = (f(y + inc_j e_j) - f0) / inc_j.  Columns are
 // written to the LDS matrix area (padding entries keep the identity), then
-// each lane reads its row.  Costs n + 1 right-hand sides.
+// read by the lanes.  Costs n + 1 right-hand sides.
 template <int S, typename LT, bool ABC, bool TH, bool LOC, int G>
 __device__ __forceinline__ void dq_matrix(Mat<S, LT, G> &a, const MechDev &m, const Lds &L, const Grp<G> &W,
                                           double y, double Fi, double gamma, double h, double ewt,

@@ -183,6 +183,11 @@ const void *pair_kernel(bool fp32, int minw, int taba) {
   return t[fp32 ? 1 : 0][taba];
 }
 
+// Waves per SIMD the adjoint kernels' registers must allow (1: compiler's
+// choice).  At 21 species the tiled elimination takes 100 to 110 registers, so
+// four; without a bound it took 153.
+__host__ __device__ constexpr int adjoint_waves(int S) { return S > 32 ? 2 : S > 16 ? 4 : 1; }
+
 // Adjoint sweep over a full record: one wave per cell.  A step is the Newton
 // matrix of M^T, its inverse, one solve and two passes over the reactions; bound
 // by the issue of those instructions, half of them the inverse's.  ABC as in
@@ -191,11 +196,6 @@ const void *pair_kernel(bool fp32, int minw, int taba) {
 // general -> ABC -> with the next step's row loaded ahead and its coefficients by
 // lane (adjoint_steps): 21 species, 4,096 cells 30.2 -> 29.1 -> 28.4 ms, 256 cells
 // 10.7 -> 10.0 -> 9.8; 53 species, 512 cells 45.7 -> 43.2 -> 42.5.
-// Waves per SIMD the adjoint kernels' registers must allow (1: compiler's
-// choice).  At 21 species the tiled elimination takes 100 to 110 registers, so
-// four; without a bound it took 153.
-__host__ __device__ constexpr int adjoint_waves(int S) { return S > 32 ? 2 : S > 16 ? 4 : 1; }
-
 template <int S, bool ABC>
 __global__ void __launch_bounds__(256, adjoint_waves(S)) k_adjoint(Params P) {
   extern __shared__ double smem[];

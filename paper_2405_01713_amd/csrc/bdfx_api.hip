@@ -3,7 +3,7 @@
 // Owns the context (device, stream, plan, bound buffers) and the
 // device-resident mechanism tables; builds the reaction slot words and the
 // lane-major analytic-Jacobian term tables from the stoichiometry; launches
-// the per-size integrator kernels (one wavefront per cell).  Nothing here allocates device memory after
+// the per-size integrator kernels.  Nothing here allocates device memory after
 // bdfx_bind() (the paper's memory-pool lesson, Sec. 4.3.1), so integrate and
 // perturb can be captured into a HIP graph by the caller.
 #include <hip/hip_runtime.h>
@@ -788,8 +788,8 @@ static int configure_bin(bdfx_ctx ctx, Bin &b) {
 // both mechanisms are isothermal A + B <=> C mechanisms on the direct solver
 // with the analytic Jacobian, their padded sizes form a compiled pair, an A
 // area holds a B cell and some shape keeps A's resident waves; otherwise
-// ctx->pair stays null and the bins are launched one after the other (one
-// cell per wave in either case).
+// ctx->pair stays null and the bins are launched one after the other, each in
+// its own form.
 static int configure_pair(bdfx_ctx ctx) {
   ctx->pair = nullptr;
   if (ctx->opt.scheduler != BDFX_SCHED_FUSED || ctx->bins.size() != 2 || ctx->pair_off)
