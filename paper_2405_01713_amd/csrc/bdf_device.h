@@ -1133,7 +1133,11 @@ __device__ __forceinline__ void newton_matrix_thermal(Mat<S, LT, G> &a, const Me
         int col;
         double d;
         if (side == 2) {
+          // (an index the optimizer cannot trace: it replaces an addition of all
+          // lanes to one known address by a sum over the lanes added at once, so
+          // that the last bits hung on whether it could see that)
           col = ns;
+          asm volatile("" : "+v"(col));
           d = q * m.EaR[r] * rT * rT;
         } else {
           col = sp2[side][c];

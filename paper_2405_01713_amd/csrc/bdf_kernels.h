@@ -55,8 +55,8 @@ template <int S, typename LT, int MINW, int TAB, int G, bool ABC, bool TH,
           int LIN = kLinAnalytic, bool LOCK = false>
 __global__ void __launch_bounds__(LOCK ? lock_threads(S, sizeof(LT)) : 256, MINW) k_integrate(Params P) {
   extern __shared__ double smem[];
-  // (a scalar LDS base; the non-isothermal kernels keep the form in which their
-  // energy sums are fused as they always were: with it the last bits moved)
+  // (a scalar LDS base; not in the non-isothermal kernels, ms vector / scalar: 9
+  // species, 300 cells 3.32 / 3.47, 21 species with GMRES 66.7 / 73.3)
   const int wib = TH ? static_cast<int>(threadIdx.x / kWave) : uni(static_cast<int>(threadIdx.x / kWave));
   const Grp<G> W(threadIdx.x & (kWave - 1));
   const int wpb = blockDim.x / kWave;
